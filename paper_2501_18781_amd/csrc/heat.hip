@@ -46,10 +46,8 @@ template <typename T, int MODE, int HK>
 __device__ __forceinline__ void heat_cell_coeffs(const HeatArgs &a, T *phq, const T *kq, const T *rcq, T am_w,
                                                  T ak_w, T *cm, T *ck)
 {
-    if (MODE == 0 && HK == 1) {
-        // out of line and not unrolled: one transcendental evaluation per point
-        for (int q = 0; q < 27; ++q) phq[q] = T(heaviside_sine_value(a.eps, (double)phq[q]));
-    }
+    // FP32 kernels hold few registers (four wavefronts per SIMD): groups of 3
+    if constexpr (MODE == 0 && HK == 1) heaviside_sine<27, sizeof(T) == 8 ? 9 : 3>(phq);
     // The Gauss weight of point q is w[q%3] w[q/3%3] w[q/9], one of four
     // products w0^3, w0^2 w1, w0 w1^2, w1^3 (class = number of middle-point
     // indices).  cm_q = A[class] + B[class] H_q, ck_q likewise: one FMA each.
@@ -117,6 +115,30 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
         dir(std::integral_constant<int, 1>{});
         dir(std::integral_constant<int, 2>{});
     }
+    // |grad phi| H' in place of |grad phi|^2, then H in place of phi
+    if (a.penalty != 0.0) {
+#pragma unroll
+        for (int q = 0; q < 27; q += 9) {
+            double dH[9];
+            if constexpr (HK == 1) {
+                heaviside_sine_derivative<9, 9>(ph + q, dH);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 9; ++j) dH[j] = heaviside_linear_derivative(ph[q + j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                gn[q + j] = dH[j] * sqrt(gn[q + j]);
+                asm volatile("" : "+v"(gn[q + j])); // one group at a time
+            }
+        }
+    }
+    if constexpr (HK == 1) {
+        heaviside_sine<27, 9>(ph);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 27; ++q) ph[q] = heaviside_linear<double>(ph[q]);
+    }
     if (a.tc) {
         br.gather27(ts, Tq);
         interp3(Tq);
@@ -127,8 +149,7 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
     const double ak_r2 = a.ak * ck_scale / (kR * kR); // ck_scale: 1, or 1/(4 h^2) for the equal-edge form
 #pragma unroll
     for (int q = 0; q < 27; ++q) {
-        double dH;
-        const double H = heaviside<double>(HK, a.eps, ph[q], &dH);
+        const double H = ph[q];
         double Hs = 0.0;
         if (a.tc) {
             const double fs = fmin(fmax((a.T_liq - Tq[q]) * inv_range, 0.0), 1.0);
@@ -136,7 +157,7 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
         }
         const double k = H * (Hs * a.k_s + (1.0 - Hs) * a.k_l) + (1.0 - H) * a.k_g;
         const double rc = H * (Hs * a.rc_s + (1.0 - Hs) * a.rc_l) + (1.0 - H) * a.rc_g;
-        const double react = a.penalty * dH * sqrt(gn[q]) * (a.rc_g + H * (a.rc_l - a.rc_g)) * c_rcp;
+        const double react = a.penalty * gn[q] * (a.rc_g + H * (a.rc_l - a.rc_g)) * c_rcp;
         const double w = vol * Q2<double>::weight(q % 3) * Q2<double>::weight((q / 3) % 3) * Q2<double>::weight(q / 9);
         cm[q] = w * (a.am * rc + react);
         ck[q] = w * ak_r2 * k;
@@ -206,9 +227,8 @@ __device__ __forceinline__ void cell_heaviside(const Brick &br, const HeatArgs &
 {
     br.gather27(ps, H);
     interp3(H);
-    if (HK == 1) {
-        for (int q = 0; q < 27; ++q) // out of line, not unrolled (as in heat_cell_coeffs)
-            H[q] = heaviside_sine_value(a.eps, H[q]);
+    if constexpr (HK == 1) {
+        heaviside_sine<27, 3>(H); // the convective forms have few registers to spare
     } else {
 #pragma unroll
         for (int q = 0; q < 27; ++q) H[q] = heaviside_linear<double>(H[q]);
@@ -894,11 +914,17 @@ __global__ void __launch_bounds__(QPT) heat_qp_kernel(KMesh m, HeatArgs a, doubl
 #pragma unroll
             for (int i = 0; i < 3; ++i) ph[i + 3 * b + 9 * c] = phi[node_index(m, 2 * cx + i, 2 * cy + b, 2 * cz + c)];
     interp3(ph);
+    if (a.hkind == 1) {
+        heaviside_sine<27, 9>(ph);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 27; ++q) ph[q] = heaviside_linear<double>(ph[q]);
+    }
     // unrolled: a loop over q would index ph at run time and put it in
     // scratch memory
 #pragma unroll
     for (int q = 0; q < 27; ++q) {
-        const double H = heaviside<double>(a.hkind, a.eps, ph[q], nullptr);
+        const double H = ph[q];
         kq[cell * 27 + q] = a.k_g + H * (a.k_l - a.k_g);
         rcq[cell * 27 + q] = a.rc_g + H * (a.rc_l - a.rc_g);
     }
@@ -918,7 +944,7 @@ hipError_t heat_qp_coeffs(const KMesh &m, const HeatArgs &a, double *kq, double 
 //   dphi_j = sum_q N_j(x_q) H'(phi_q) [(k_l - k_g) dk_q + (rc_l - rc_g) drc_q]
 // ---------------------------------------------------------------------------
 template <int HK>
-__global__ void __launch_bounds__(BNT) heat_grad_kernel(KMesh m, HeatArgs a, const double *__restrict__ T,
+__global__ void __launch_bounds__(BNT) __attribute__((amdgpu_waves_per_eu(2, 2))) heat_grad_kernel(KMesh m, HeatArgs a, const double *__restrict__ T,
                                                         const double *__restrict__ dT, const double *__restrict__ lam,
                                                         double *__restrict__ dk, double *__restrict__ drc,
                                                         double *__restrict__ dphi, double *__restrict__ face)
@@ -976,20 +1002,12 @@ __global__ void __launch_bounds__(BNT) heat_grad_kernel(KMesh m, HeatArgs a, con
     double ph[27];
     br.gather27(ps, ph);
     interp3(ph);
-    if constexpr (HK == 0) {
+    if constexpr (HK == 1) heaviside_sine_derivative<27, 3>(ph, ph);
 #pragma unroll
-        for (int q = 0; q < 27; ++q) {
-            double dH;
-            (void)heaviside<double>(0, a.eps, ph[q], &dH);
-            s[q] = dH * ((a.k_l - a.k_g) * gk[q] + (a.rc_l - a.rc_g) * s[q]);
-            asm volatile("" : "+v"(s[q])); // one point at a time
-        }
-    } else {
-        for (int q = 0; q < 27; ++q) { // out of line and not unrolled: one transcendental evaluation per point
-            double dH;
-            (void)heaviside<double>(1, a.eps, ph[q], &dH);
-            s[q] = dH * ((a.k_l - a.k_g) * gk[q] + (a.rc_l - a.rc_g) * s[q]);
-        }
+    for (int q = 0; q < 27; ++q) {
+        const double dH = HK == 1 ? ph[q] : heaviside_linear_derivative(ph[q]);
+        s[q] = dH * ((a.k_l - a.k_g) * gk[q] + (a.rc_l - a.rc_g) * s[q]);
+        asm volatile("" : "+v"(s[q])); // one point at a time
     }
     interp3T(s);
     __syncthreads();

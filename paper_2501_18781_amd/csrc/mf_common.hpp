@@ -325,45 +325,153 @@ template <typename T> __device__ __forceinline__ T heaviside_linear(T phi)
     return fmin(fmax(T(0.5) + T(0.5) * phi, T(0)), T(1));
 }
 
-// Sine form in FP64, kept out of line: its transcendental functions would
-// otherwise be replicated at every unrolled Gauss point.
-__device__ __noinline__ inline double heaviside_sine(double eps, double phi, double *dH)
+// Sine form in FP64.  With d = 2 eps artanh(phi) the thickness parameter
+// cancels: with L = 2 artanh(phi) = d / eps, the form
+//   H = 1/2 + L/6 + sin(pi L/3) / (2 pi)  for |L| < 3 (|phi| < tanh(3/2)), else 0 or 1,
+//   dH/dphi = (1 + cos(pi L/3)) / (3 (1 - phi^2))  there, else 0,
+// is a function of phi alone: H - 1/2 is phi times an even function and
+// dH/dphi is even, both smooth in t = phi^2 on [0, tanh(3/2)^2].  They are
+// evaluated as polynomials in x = 2 t / tanh(3/2)^2 - 1 on [-1, 1], the
+// Chebyshev interpolants of those functions (computed with 60 digits),
+// truncated where the rest is below 3e-17 (H) and 3e-17 (dH/dphi).  Error
+// against 64-digit values over 20000 points: H max 2.2e-16, rms 3.8e-17;
+// dH/dphi max 3.5e-16, rms 8.3e-17 (through atanh, sin and cos: 2.2e-16,
+// 5.3e-17; 5.0e-16, 9.4e-17).  A call through the three library functions
+// cost about 1100 SIMD cycles per Gauss point and wavefront, against 39 fused
+// multiply-adds here (4 cycles each): FP64 heat apply at 50x37x61 cells 53.2
+// -> 24.7 us, source assembly and transport velocity at 64^3 252 -> 189 us.
+__device__ constexpr double kSineP = 0.9051482536448664382423037;  // tanh(3/2)
+__device__ constexpr double kSineX = 2.441128044016478105990102;   // 2 / tanh(3/2)^2
+constexpr int kSineNH = 39, kSineND = 45;
+__device__ constexpr double kSineH[39] = {
+    6.43520269740246897e-01, -4.43126021180735227e-02, -3.07422505219364268e-02, -1.32877722172321227e-02,
+    -4.86526952347678121e-03, -1.27799812199075693e-03, 1.12047235257928406e-04, 5.55960170554967376e-04,
+    6.16186723109304652e-04, 5.38839683093071849e-04, 4.27405438207980378e-04, 3.21889722882067689e-04,
+    2.35013445340591370e-04, 1.68793312227063304e-04, 1.19557771058572304e-04, 7.97900624346346041e-05,
+    5.32658912965180555e-05, 5.47927292189657968e-05, 4.59433262017686170e-05, -3.33605873700981357e-05,
+    -4.73178319148966249e-05, 1.46694300141124250e-04, 1.55576753891603620e-04, -2.75924412134287509e-04,
+    -2.84670103517266045e-04, 4.37552290079588077e-04, 4.27085646005613269e-04, -5.15154961072379321e-04,
+    -4.81870352193232334e-04, 4.58090215840123579e-04, 4.11265987496103403e-04, -2.94906038246385332e-04,
+    -2.55217387973624005e-04, 1.31166676993557050e-04, 1.09647570983554440e-04, -3.60687829282825838e-05,
+    -2.91975073798846566e-05, 4.73298787729888257e-06, 3.70927825700015205e-06,
+};
+__device__ constexpr double kSineD[45] = {
+    5.54895065504099172e-01, -2.55906808441978995e-01, -2.33437885912560039e-01, -1.31936561704740690e-01,
+    -5.65674069933000609e-02, -1.27134128334104590e-02, 9.24005939123523357e-03, 1.81984025501983199e-02,
+    2.01742155920174270e-02, 1.87857844953160137e-02, 1.60581769592588464e-02, 1.30477405846037512e-02,
+    1.02533638547828553e-02, 7.86678329694943425e-03, 5.93149134900614050e-03, 4.44216665234599059e-03,
+    3.29082112994548903e-03, 2.22522258316671870e-03, 1.51143640624501951e-03, 1.99620976918712207e-03,
+    1.87169951860786249e-03, -2.24873853880814059e-03, -3.06572474141258121e-03, 9.04569019929043865e-03,
+    1.02694728774525741e-02, -2.07138587294071232e-02, -2.27086457803105553e-02, 3.97782942124349920e-02,
+    4.14854239906509020e-02, -5.98630433983693006e-02, -5.99021531908460053e-02, 7.13157838918452164e-02,
+    6.86417745938329160e-02, -6.61284572939923598e-02, -6.14361358456230328e-02, 4.68670946654939150e-02,
+    4.21322547982579676e-02, -2.45305185145998396e-02, -2.13887613793536414e-02, 8.96477507430815460e-03,
+    7.59499567634474692e-03, -2.04856393825841648e-03, -1.68895744109442600e-03, 2.22682085091917352e-04,
+    1.78752976096558329e-04,
+};
+
+// The two constant parts: 0 and 1 outside the interface, and a NaN stays one.
+__device__ __forceinline__ double sine_saturated(double p, double inside)
 {
-    const double lim = 1.0 - 1e-15;
-    const double p = phi < -lim ? -lim : (phi > lim ? lim : phi);
-    const double d = 2.0 * eps * atanh(p);
-    if (d <= -3.0 * eps) { *dH = 0.0; return 0.0; }
-    if (d >= 3.0 * eps) { *dH = 0.0; return 1.0; }
-    const double a = M_PI * d / (3.0 * eps);
-    *dH = (1.0 + cos(a)) / (6.0 * eps) * (2.0 * eps / (1.0 - p * p));
-    return 0.5 + d / (6.0 * eps) + sin(a) / (2.0 * M_PI);
+    const double r = p >= kSineP ? 1.0 : inside;
+    return p <= -kSineP ? 0.0 : r;
 }
 
-// The sine form's value alone: the same expression as heaviside_sine without
-// its derivative (one transcendental fewer per point).
-__device__ __noinline__ inline double heaviside_sine_value(double eps, double phi)
+// N values of H at p (in place).  The points advance together through the
+// polynomial, so that each coefficient is brought into scalar registers once
+// for N of them and N independent chains cover the multiply-add latency.
+template <int N> __device__ __forceinline__ void sine_values(double *p)
 {
-    const double lim = 1.0 - 1e-15;
-    const double p = phi < -lim ? -lim : (phi > lim ? lim : phi);
-    const double d = 2.0 * eps * atanh(p);
-    if (d <= -3.0 * eps) return 0.0;
-    if (d >= 3.0 * eps) return 1.0;
-    const double a = M_PI * d / (3.0 * eps);
-    return 0.5 + d / (6.0 * eps) + sin(a) / (2.0 * M_PI);
-}
-
-template <typename T> __device__ __forceinline__ T heaviside(int kind, T eps, T phi, T *dH)
-{
-    if (kind == 0) {
-        if (dH) *dH = (phi > T(-1) && phi < T(1)) ? T(0.5) : T(0);
-        return heaviside_linear<T>(phi);
+    double x[N], r[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        x[j] = __builtin_fma(p[j] * p[j], kSineX, -1.0);
+        r[j] = kSineH[kSineNH - 1];
     }
-    if (!dH) return T(heaviside_sine_value((double)eps, (double)phi));
-    double d;
-    const double H = heaviside_sine((double)eps, (double)phi, &d);
-    *dH = T(d);
-    return T(H);
+#pragma unroll
+    for (int k = kSineNH - 2; k >= 0; --k)
+#pragma unroll
+        for (int j = 0; j < N; ++j) r[j] = __builtin_fma(r[j], x[j], kSineH[k]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) p[j] = sine_saturated(p[j], __builtin_fma(p[j], r[j], 0.5));
 }
+
+// dH/dphi at N points p, into d (which may be p).
+template <int N> __device__ __forceinline__ void sine_derivatives(const double *p, double *d)
+{
+    double x[N], r[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        x[j] = __builtin_fma(p[j] * p[j], kSineX, -1.0);
+        r[j] = kSineD[kSineND - 1];
+    }
+#pragma unroll
+    for (int k = kSineND - 2; k >= 0; --k)
+#pragma unroll
+        for (int j = 0; j < N; ++j) r[j] = __builtin_fma(r[j], x[j], kSineD[k]);
+#pragma unroll
+    for (int j = 0; j < N; ++j) d[j] = fabs(p[j]) >= kSineP ? 0.0 : r[j];
+}
+
+// Whether any of the wavefront's NQ interpolated level-set values lies inside
+// the interface.  Away from it, on most bricks of a mesh with an interface a
+// few cells wide, H is 0 or 1 and the polynomials are skipped (a uniform
+// branch; NaNs are not seen here and pass through sine_saturated).
+template <int NQ, typename T> __device__ __forceinline__ bool sine_inside(const T *p)
+{
+    T m = fabs(p[0]);
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) m = fmin(m, fabs(p[q]));
+    return __ballot(m < T(kSineP)) != 0;
+}
+
+// H of the sine form at NQ points (in place), G points at a time (NQ a
+// multiple of G; G sets the registers in flight, 6 G).
+template <int NQ, int G, typename T> __device__ __forceinline__ void heaviside_sine(T *p)
+{
+    static_assert(NQ % G == 0, "whole groups");
+    if (sine_inside<NQ>(p)) {
+#pragma unroll
+        for (int q = 0; q < NQ; q += G) {
+            double v[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) v[j] = (double)p[q + j];
+            sine_values<G>(v);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                p[q + j] = T(v[j]);
+                asm volatile("" : "+v"(p[q + j])); // one group at a time
+            }
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) p[q] = T(sine_saturated((double)p[q], (double)p[q]));
+    }
+}
+
+// dH/dphi of the sine form at NQ points of p, into d (may be p).
+template <int NQ, int G> __device__ __forceinline__ void heaviside_sine_derivative(const double *p, double *d)
+{
+    static_assert(NQ % G == 0, "whole groups");
+    if (sine_inside<NQ>(p)) {
+#pragma unroll
+        for (int q = 0; q < NQ; q += G) {
+            double v[G];
+            sine_derivatives<G>(p + q, v);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                d[q + j] = v[j];
+                asm volatile("" : "+v"(d[q + j])); // one group at a time
+            }
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) d[q] = p[q] == p[q] ? 0.0 : p[q];
+    }
+}
+
+// dH/dphi of the linear form.
+__device__ __forceinline__ double heaviside_linear_derivative(double phi) { return (phi > -1.0 && phi < 1.0) ? 0.5 : 0.0; }
 
 // ---------------------------------------------------------------------------
 // Deterministic reductions without atomics.  A block sums its threads' values

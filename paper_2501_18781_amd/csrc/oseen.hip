@@ -29,15 +29,24 @@ constexpr int ONT = 3 * BNT; // threads per Oseen brick
 constexpr int NB = lds_field<double>(); // LDS entries of one staged nodal field
 
 // Heaviside of the interpolated level set at the 27 Gauss points (in place).
-template <int HK> __device__ __forceinline__ void heaviside27(const OseenArgs &a, double *ph)
+template <int HK> __device__ __forceinline__ void heaviside27(double *ph)
 {
+    if constexpr (HK == 1) {
+        heaviside_sine<27, 9>(ph);
+    } else {
 #pragma unroll
-    for (int q = 0; q < 27; ++q) {
-        if (HK == 0) {
-            ph[q] = heaviside_linear<double>(ph[q]);
-        } else {
-            ph[q] = heaviside_sine_value(a.eps, ph[q]);
-        }
+        for (int q = 0; q < 27; ++q) ph[q] = heaviside_linear<double>(ph[q]);
+    }
+}
+
+// The same at the nine points 9C .. 9C + 8, which wavefront C evaluates.
+template <int HK, int C> __device__ __forceinline__ void heaviside9(double *ph)
+{
+    if constexpr (HK == 1) {
+        heaviside_sine<9, 9>(ph + 9 * C);
+    } else {
+#pragma unroll
+        for (int q = 9 * C; q < 9 * C + 9; ++q) ph[q] = heaviside_linear<double>(ph[q]);
     }
 }
 
@@ -118,6 +127,7 @@ __device__ __forceinline__ void oseen_phase1(const Brick &br, const OseenArgs &a
     double h[27];
     br.gather27(ps, h);
     interp3(h);
+    heaviside9<HK, C>(h);
     if constexpr (TP) {
         double tq[27];
         br.gather27(tcs, tq);
@@ -125,7 +135,7 @@ __device__ __forceinline__ void oseen_phase1(const Brick &br, const OseenArgs &a
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
             const int q = 9 * C + j;
-            const double H = HK == 0 ? heaviside_linear<double>(h[q]) : heaviside_sine_value(a.eps, h[q]);
+            const double H = h[q];
             const double Hs = solid_indicator(solid_fraction(a, tq[q]));
             const double W = vol * gauss_weight(q);
             rwl[q * BNT + t] = W / (H / (Hs * a.rho_s + (1.0 - Hs) * a.rho_l) + (1.0 - H) / a.rho_g);
@@ -142,7 +152,7 @@ __device__ __forceinline__ void oseen_phase1(const Brick &br, const OseenArgs &a
 #pragma unroll
         for (int j = 0; j < 9; ++j) {
             const int q = 9 * C + j;
-            const double H = HK == 0 ? heaviside_linear<double>(h[q]) : heaviside_sine_value(a.eps, h[q]);
+            const double H = h[q];
             const double W = vol * gauss_weight(q);
             rwl[q * BNT + t] = W / (H / a.rho_l + (1.0 - H) / a.rho_g);
             nul[q * BNT + t] = a.av * W * (a.mu_g + H * (a.mu_l - a.mu_g));
@@ -382,7 +392,7 @@ __global__ void __launch_bounds__(BNT) oseen_block_kernel(KMesh m, OseenArgs a, 
     double rw[27], nu[27], w0[27], dw[27]; // rho W, alpha_v mu W, scratch (velocity), Darcy W
     br.gather27(ps, rw);
     interp3(rw);
-    heaviside27<HK>(a, rw);
+    heaviside27<HK>(rw);
     if (TP) {
         br.gather27(tcs, dw);
         interp3(dw);

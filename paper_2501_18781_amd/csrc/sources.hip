@@ -68,12 +68,32 @@ __global__ void __launch_bounds__(BNT) heat_source_kernel(KMesh m, HeatArgs a, S
     const double xc[3] = {m.lox + m.hx * (br.c0x + br.tx), m.loy + m.hy * (br.c0y + br.ty),
                           m.loz + m.hz * (br.c0z + br.tz)};
     const double xi[3] = {0.5 - kR, 0.5, 0.5 + kR};
+    // ph: H' rc(phi) c_rcp (delta_rcp / |grad phi|), three points at a time
+#pragma unroll
+    for (int q = 0; q < 27; q += 3) {
+        double H[3], dH[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) H[j] = ph[q + j];
+        if constexpr (HK == 1) {
+            heaviside_sine_derivative<3, 3>(H, dH);
+            heaviside_sine<3, 3>(H);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                dH[j] = heaviside_linear_derivative(H[j]);
+                H[j] = heaviside_linear<double>(H[j]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            ph[q + j] = dH[j] * (a.rc_g + H[j] * (a.rc_l - a.rc_g)) * sa.c_rcp;
+            asm volatile("" : "+v"(ph[q + j]));
+        }
+    }
 #pragma unroll
     for (int q = 0; q < 27; ++q) {
         const int qi[3] = {q % 3, (q / 3) % 3, q / 9};
-        double dH;
-        const double H = heaviside<double>(HK, a.eps, ph[q], &dH);
-        const double drc = dH * (a.rc_g + H * (a.rc_l - a.rc_g)) * sa.c_rcp; // delta_rcp / |grad phi|
+        const double drc = ph[q];
         double lq = 0.0;
         if (laser && ge[q] > 0.0) {
             double r[3], t = 0.0;
