@@ -33,7 +33,21 @@ struct KMesh {
     unsigned dirichlet; // face bits
     double hx, hy, hz;  // cell edges
     double lox, loy, loz;
+    // floor(2^32 / d) (all ones for d = 1) of the divisors of a brick's index:
+    // bricks along x and y, slabs along x (see udiv)
+    unsigned rbx, rby, rsx;
 };
+
+// n / d for a uniform d with r = floor(2^32 / d): the product's high word is
+// n / d or one less for every n < 2^32, corrected once.  Five scalar
+// instructions, where the compiler's division takes a chain of about 25
+// through a vector reciprocal.
+__host__ __device__ inline unsigned udiv_reciprocal(unsigned d) { return d == 1 ? 0xFFFFFFFFu : (unsigned)(0x100000000ull / d); }
+__device__ __forceinline__ unsigned udiv(unsigned n, unsigned d, unsigned r)
+{
+    const unsigned q = __umulhi(n, r);
+    return q + (n - q * d >= d ? 1u : 0u);
+}
 
 __device__ __forceinline__ bool node_constrained(const KMesh &m, int i, int j, int k)
 {
@@ -117,6 +131,13 @@ template <typename T> struct Q2 {
         o0 += T(-3) * i0 - i1 + i2;
         o1 += T(4) * (i0 - i2);
         o2 += T(3) * i2 + (i1 - i0);
+    }
+    // out += 2 D''^T in
+    static __device__ __forceinline__ void deriv2T_acc2(T i0, T i1, T i2, T &o0, T &o1, T &o2)
+    {
+        o0 += T(-6) * i0 - T(2) * (i1 - i2);
+        o1 += T(8) * (i0 - i2);
+        o2 += T(6) * i2 + T(2) * (i1 - i0);
     }
     static __device__ __forceinline__ T weight(int q) { return q == 1 ? w1 : w0; }
 };

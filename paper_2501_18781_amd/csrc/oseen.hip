@@ -8,10 +8,11 @@
 // (the last term equals 2 mu eps(u):eps(v)).  The transpose moves the
 // convective term onto the test function: alpha_c rho u_c (u0.grad) v_c.
 //
-// Work decomposition: one workgroup of three wavefronts per brick of 4x4x4
-// cells (brick.hpp); wavefront c takes velocity component c, one thread per
-// cell.  Nodal x (3 components), u0 (3 components) and phi are staged in LDS
-// once for the three.  Per cell and component:
+// Work decomposition: one workgroup of four wavefronts per brick of 4x4x4
+// cells (brick.hpp), one thread per cell.  Wavefront c < 3 computes velocity
+// component c, wavefront 3 the coefficients at the Gauss points.  Nodal x (3
+// components), u0 (3 components) and phi are staged in LDS once for the four.
+// Per cell and component:
 //   acc = alpha_m rho W u_c                                  (Gauss values)
 //       + alpha_c rho W sum_d u0_d d_d u_c                   (forward)
 //   acc += sum_d D_d^T [ W mu alpha_v (d_d u_c + d_c u_d)    (viscous)
@@ -25,7 +26,7 @@
 
 namespace mf {
 
-constexpr int ONT = 3 * BNT; // threads per Oseen brick
+constexpr int ONT = 4 * BNT; // threads per Oseen brick: three components and the coefficients
 constexpr int NB = lds_field<double>(); // LDS entries of one staged nodal field
 
 // Heaviside of the interpolated level set at the 27 Gauss points (in place).
@@ -39,62 +40,9 @@ template <int HK> __device__ __forceinline__ void heaviside27(double *ph)
     }
 }
 
-// The same at the nine points 9C .. 9C + 8, which wavefront C evaluates.
-template <int HK, int C> __device__ __forceinline__ void heaviside9(double *ph)
-{
-    if constexpr (HK == 1) {
-        heaviside_sine<9, 9>(ph + 9 * C);
-    } else {
-#pragma unroll
-        for (int q = 9 * C; q < 9 * C + 9; ++q) ph[q] = heaviside_linear<double>(ph[q]);
-    }
-}
-
 __device__ __forceinline__ double gauss_weight(int q)
 {
     return Q2<double>::weight(q % 3) * Q2<double>::weight((q / 3) % 3) * Q2<double>::weight(q / 9);
-}
-
-// d_c applied line by line to the Gauss values v (in place), scaled by s.
-template <int DIR> __device__ __forceinline__ void deriv_inplace(double *v, double s)
-{
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            const int i0 = lidx<DIR>(0, m, n), i1 = lidx<DIR>(1, m, n), i2 = lidx<DIR>(2, m, n);
-            double t0, t1, t2;
-            Q2<double>::deriv(v[i0], v[i1], v[i2], t0, t1, t2);
-            v[i0] = s * t0;
-            v[i1] = s * t1;
-            v[i2] = s * t2;
-        }
-}
-
-// Viscous part along DIR: g = nu .* (s d_DIR u + e), acc += s D_DIR^T g, line
-// by line (e = d_c u_d already scaled, or null for the d = c term with factor 2).
-template <int DIR, bool TWICE>
-__device__ __forceinline__ void visc_dir(const double *u, const double *nu, const double *e, double s, double *acc)
-{
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            const int i0 = lidx<DIR>(0, m, n), i1 = lidx<DIR>(1, m, n), i2 = lidx<DIR>(2, m, n);
-            double t0, t1, t2;
-            Q2<double>::deriv(u[i0], u[i1], u[i2], t0, t1, t2);
-            double g0, g1, g2;
-            if (TWICE) {
-                g0 = 2.0 * s * nu[i0] * t0;
-                g1 = 2.0 * s * nu[i1] * t1;
-                g2 = 2.0 * s * nu[i2] * t2;
-            } else {
-                g0 = nu[i0] * (s * t0 + e[i0]);
-                g1 = nu[i1] * (s * t1 + e[i1]);
-                g2 = nu[i2] * (s * t2 + e[i2]);
-            }
-            Q2<double>::derivT_acc(s * g0, s * g1, s * g2, acc[i0], acc[i1], acc[i2]);
-        }
 }
 
 // Solid fraction (eq. solid_fraction) and smooth indicator H_s (eq. heaviside_sl).
@@ -109,158 +57,226 @@ __device__ __forceinline__ double solid_indicator(double fs) { return fs * fs * 
 // consecutive lanes in consecutive banks.
 constexpr int GQ = 27 * BNT; // doubles of one shared Gauss-point field
 
-// Phase 1 of component C on one cell (every wavefront of the brick runs it
-// for its own C, on the staged nodal fields):
-//   u   = S x_C at the Gauss points (returned in u);
-//   w0  = S u0_C at the Gauss points (returned in w0, shared after a barrier);
-//   the coefficients rho W and alpha_v mu W at the nine Gauss points
-//   9C .. 9C + 8 (the three wavefronts split the 27 points), written to the
-//   shared fields rwl and nul;
-//   acc = Darcy weight * u with three phases (TP), untouched otherwise.
-template <int C, int HK, bool TP>
-__device__ __forceinline__ void oseen_phase1(const Brick &br, const OseenArgs &a, const KMesh &m, const double *stage,
-                                             double *rwl, double *nul, double *u, double *w0, double *acc)
+// Index of the Gauss point with position i along direction A, j along B and
+// k along the third.
+template <int A, int B> __device__ __forceinline__ constexpr int qidx(int i, int j, int k)
 {
-    const double *ps = stage, *us = stage + NB, *u0s = stage + 4 * NB, *tcs = stage + 7 * NB;
+    constexpr int st[3] = {1, 3, 9};
+    return i * st[A] + j * st[B] + k * st[3 - A - B];
+}
+
+// Scales of the derivative passes, which work with the integer form
+// D'' = 2 r D: d/dx_d = s[d] D''_d.  On a mesh with equal cell edges (ISO)
+// the three are the same number, which goes into the coefficients (ac s into
+// the convection, s^2 into the viscosity), so the passes need no scaling.
+struct OseenScales {
+    double s[3];
+    __device__ __forceinline__ explicit OseenScales(const KMesh &m)
+    {
+        s[0] = 0.5 / (kR * m.hx);
+        s[1] = 0.5 / (kR * m.hy);
+        s[2] = 0.5 / (kR * m.hz);
+    }
+};
+
+// The coefficients of one cell at its 27 Gauss points (wavefront 3): rho W
+// into rwl, the Darcy weight W C fs^2 / ((1 - fs)^3 + b) into dwl (three
+// phases), alpha_v mu W (times s^2 with ISO) into nu.
+template <int HK, bool TP, bool ISO>
+__device__ __forceinline__ void oseen_coeffs(const Brick &br, const OseenArgs &a, const KMesh &m, const double *ps,
+                                             const double *tcs, double *rwl, double *dwl, double *nu)
+{
     const double vol = m.hx * m.hy * m.hz;
+    const OseenScales sc(m);
+    const double avs = ISO ? a.av * sc.s[0] * sc.s[0] : a.av;
     const int t = br.t;
-    double h[27];
-    br.gather27(ps, h);
-    interp3(h);
-    heaviside9<HK, C>(h);
+    const double irl = 1.0 / a.rho_l, irg = 1.0 / a.rho_g;
+    br.gather27(ps, nu);
+    interp3(nu);
+    heaviside27<HK>(nu);
+    // Groups of 3 (three phases) or 9 points: enough independent divisions
+    // in flight to cover their latency (27 one after the other held the
+    // component wavefronts up for 9000 cycles), without spilling.
     if constexpr (TP) {
+        const double inv_range = 1.0 / (a.T_liq - a.T_sol);
         double tq[27];
         br.gather27(tcs, tq);
         interp3(tq);
 #pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const int q = 9 * C + j;
-            const double H = h[q];
-            const double Hs = solid_indicator(solid_fraction(a, tq[q]));
-            const double W = vol * gauss_weight(q);
-            rwl[q * BNT + t] = W / (H / (Hs * a.rho_s + (1.0 - Hs) * a.rho_l) + (1.0 - H) / a.rho_g);
-            nul[q * BNT + t] = a.av * W * (H * (Hs * a.mu_s + (1.0 - Hs) * a.mu_l) + (1.0 - H) * a.mu_g);
-        }
-        // Darcy weight W C fs^2 / ((1 - fs)^3 + b), held in acc until u is known
+        for (int g = 0; g < 27; g += 3) {
 #pragma unroll
-        for (int q = 0; q < 27; ++q) {
-            const double fs = solid_fraction(a, tq[q]);
-            acc[q] = vol * gauss_weight(q) * a.darcy_C * fs * fs / ((1.0 - fs) * (1.0 - fs) * (1.0 - fs) + a.darcy_b);
+            for (int q = g; q < g + 3; ++q) {
+                const double H = nu[q], W = vol * gauss_weight(q);
+                const double fs = fmin(fmax((a.T_liq - tq[q]) * inv_range, 0.0), 1.0), Hs = solid_indicator(fs);
+                const double rho_sl = Hs * a.rho_s + (1.0 - Hs) * a.rho_l;
+                // 1 / (H / rho_sl + (1 - H) / rho_g) with one division
+                rwl[q * BNT + t] = W * (rho_sl / (H + (1.0 - H) * irg * rho_sl));
+                nu[q] = avs * W * (H * (Hs * a.mu_s + (1.0 - Hs) * a.mu_l) + (1.0 - H) * a.mu_g);
+                dwl[q * BNT + t] = W * a.darcy_C * fs * fs / ((1.0 - fs) * (1.0 - fs) * (1.0 - fs) + a.darcy_b);
+            }
+#pragma unroll
+            for (int q = g; q < g + 3; ++q) asm volatile("" : "+v"(nu[q]));
         }
-        pin27(acc);
     } else {
 #pragma unroll
-        for (int j = 0; j < 9; ++j) {
-            const int q = 9 * C + j;
-            const double H = h[q];
-            const double W = vol * gauss_weight(q);
-            rwl[q * BNT + t] = W / (H / a.rho_l + (1.0 - H) / a.rho_g);
-            nul[q * BNT + t] = a.av * W * (a.mu_g + H * (a.mu_l - a.mu_g));
+        for (int g = 0; g < 27; g += 9) {
+#pragma unroll
+            for (int q = g; q < g + 9; ++q) {
+                const double H = nu[q], W = vol * gauss_weight(q);
+                rwl[q * BNT + t] = W / (H * irl + (1.0 - H) * irg);
+                nu[q] = avs * W * (a.mu_g + H * (a.mu_l - a.mu_g));
+            }
+#pragma unroll
+            for (int q = g; q < g + 9; ++q) asm volatile("" : "+v"(nu[q]));
         }
     }
-    if constexpr (TP) pin27(acc);
-    br.gather27(us + C * NB, u);
-    interp3(u);
-    if constexpr (TP) {
-#pragma unroll
-        for (int q = 0; q < 27; ++q) acc[q] *= u[q];
-        pin27(acc);
-    }
-    pin27(u);
-    br.gather27(u0s + C * NB, w0);
-    interp3(w0);
 }
 
-// Phase 2 of component C: mass and convection with rho W from rwl and the
-// Gauss-point u0 of all three components from the shared fields w0l[d]:
-//   acc (+)= alpha_m rho W u                                   (mass)
-//   forward:   acc += alpha_c rho W sum_d u0_d d_d u
-//   transpose: acc += sum_d D_d^T (alpha_c rho W u0_d u)
-template <int C, bool TR, bool TP>
-__device__ __forceinline__ void oseen_phase2(const Brick &br, const OseenArgs &a, const KMesh &m, const double *rwl,
-                                             const double *w0l, const double *u, double *acc)
+// Mass and convection of one component, with rho W (and the Darcy weight)
+// and the Gauss-point u0 of all three components from the shared fields:
+//   forward:   acc = rho W (alpha_m u + alpha_c sum_d u0_d d_d u) + Darcy u
+//   transpose: acc = rho W alpha_m u + Darcy u + sum_d D_d^T (alpha_c rho W u0_d u)
+// Only u and acc are held in registers; the shared fields are read line by
+// line where they are used.
+template <bool TR, bool TP, bool ISO>
+__device__ __forceinline__ void oseen_convection(const Brick &br, const OseenArgs &a, const KMesh &m,
+                                                 const double *rwl, const double *dwl, const double *w0l, double *u,
+                                                 double *acc)
 {
     const int t = br.t;
-    const double sdir[3] = {1.0 / (kR * m.hx), 1.0 / (kR * m.hy), 1.0 / (kR * m.hz)};
-    double rw[27];
+    const OseenScales sc(m);
+    const double acs = a.ac * sc.s[0]; // ISO
+    double z[TR ? 27 : 1];             // transpose: alpha_c rho W u (times s with ISO)
 #pragma unroll
-    for (int q = 0; q < 27; ++q) rw[q] = rwl[q * BNT + t];
-#pragma unroll
-    for (int q = 0; q < 27; ++q) acc[q] = (TP ? acc[q] : 0.0) + a.am * rw[q] * u[q];
+    for (int q = 0; q < 27; ++q) {
+        if constexpr (TR) {
+            const double ru = rwl[q * BNT + t] * u[q];
+            acc[q] = a.am * ru;
+            if constexpr (TP) acc[q] += dwl[q * BNT + t] * u[q];
+            z[q] = (ISO ? acs : a.ac) * ru;
+        } else {
+            acc[q] = 0.0;
+        }
+    }
     auto dir = [&](auto D) {
         constexpr int d = decltype(D)::value;
-        // one direction at a time: its 27 reads are not hoisted above the
+        // one direction at a time: its reads are not hoisted above the
         // previous direction's arithmetic
         pin27(acc);
-        pin27(rw);
-        pin27((double *)u);
+        pin27(TR ? z : u);
         const double *w = w0l + d * GQ + t;
-        const double s = a.ac * sdir[d];
+        const double s = sc.s[d];
 #pragma unroll
         for (int n = 0; n < 3; ++n)
 #pragma unroll
             for (int mm = 0; mm < 3; ++mm) {
                 const int i0 = lidx<d>(0, mm, n), i1 = lidx<d>(1, mm, n), i2 = lidx<d>(2, mm, n);
+                double w0 = w[i0 * BNT], w1 = w[i1 * BNT], w2 = w[i2 * BNT];
+                if constexpr (!ISO) {
+                    w0 *= s;
+                    w1 *= s;
+                    w2 *= s;
+                }
                 if constexpr (TR) {
-                    Q2<double>::derivT_acc(s * rw[i0] * w[i0 * BNT] * u[i0], s * rw[i1] * w[i1 * BNT] * u[i1],
-                                           s * rw[i2] * w[i2 * BNT] * u[i2], acc[i0], acc[i1], acc[i2]);
+                    Q2<double>::deriv2T_acc(w0 * z[i0], w1 * z[i1], w2 * z[i2], acc[i0], acc[i1], acc[i2]);
                 } else {
                     double t0, t1, t2;
-                    Q2<double>::deriv(u[i0], u[i1], u[i2], t0, t1, t2);
-                    acc[i0] += s * rw[i0] * w[i0 * BNT] * t0;
-                    acc[i1] += s * rw[i1] * w[i1 * BNT] * t1;
-                    acc[i2] += s * rw[i2] * w[i2 * BNT] * t2;
+                    Q2<double>::deriv2(u[i0], u[i1], u[i2], t0, t1, t2);
+                    acc[i0] += w0 * t0;
+                    acc[i1] += w1 * t1;
+                    acc[i2] += w2 * t2;
                 }
             }
     };
     dir(std::integral_constant<int, 0>{});
     dir(std::integral_constant<int, 1>{});
     dir(std::integral_constant<int, 2>{});
+    if constexpr (!TR) {
+        pin27(acc);
+#pragma unroll
+        for (int q = 0; q < 27; ++q) {
+            double r = rwl[q * BNT + t] * (a.am * u[q] + (ISO ? acs : a.ac) * acc[q]);
+            if constexpr (TP) r += dwl[q * BNT + t] * u[q];
+            acc[q] = r;
+        }
+    }
 }
 
-// Phase 3 of component C: viscosity with nu = alpha_v mu W from nul and the
-// Gauss-point values of the other two components from the shared fields ul[d]:
+// Viscosity of component C with nu from nul and the Gauss-point values of the
+// other two components from the shared fields ul[d]:
 //   acc += D_C^T (2 nu d_C u_C) + sum_{d != C} D_d^T (nu (d_d u_C + d_C u_d)),
-// then y_C = S^T acc (in acc).
-template <int C>
-__device__ __forceinline__ void oseen_phase3(const Brick &br, const KMesh &m, const double *nul, const double *ul,
-                                             const double *u, double *acc)
+// plane by plane: d_C u_d is formed for the nine points of a (C, d) plane, of
+// which the plane's three lines along d take three each.
+template <int C, bool ISO>
+__device__ __forceinline__ void oseen_viscosity(const Brick &br, const KMesh &m, const double *nul, const double *ul,
+                                                double *u, double *acc)
 {
     const int t = br.t;
-    const double sdir[3] = {1.0 / (kR * m.hx), 1.0 / (kR * m.hy), 1.0 / (kR * m.hz)};
-    double nu[27];
-#pragma unroll
-    for (int q = 0; q < 27; ++q) nu[q] = nul[q * BNT + t];
-    double e[27];
-    auto cross = [&](auto D) {
+    const OseenScales sc(m);
+    auto dir = [&](auto D) {
         constexpr int d = decltype(D)::value;
         pin27(acc);
-        pin27(nu);
-        pin27((double *)u);
+        pin27(u);
         if constexpr (d == C) {
-            visc_dir<d, true>(u, nu, nullptr, sdir[d], acc);
-        } else {
+            const double f = 2.0 * sc.s[C] * sc.s[C];
 #pragma unroll
-            for (int q = 0; q < 27; ++q) e[q] = ul[d * GQ + q * BNT + t];
-            deriv_inplace<C>(e, sdir[C]); // d_C u_d
-            visc_dir<d, false>(u, nu, e, sdir[d], acc);
+            for (int n = 0; n < 3; ++n)
+#pragma unroll
+                for (int mm = 0; mm < 3; ++mm) {
+                    const int i0 = lidx<C>(0, mm, n), i1 = lidx<C>(1, mm, n), i2 = lidx<C>(2, mm, n);
+                    double t0, t1, t2;
+                    Q2<double>::deriv2(u[i0], u[i1], u[i2], t0, t1, t2);
+                    const double k0 = nul[i0 * BNT + t], k1 = nul[i1 * BNT + t], k2 = nul[i2 * BNT + t];
+                    if constexpr (ISO) Q2<double>::deriv2T_acc2(k0 * t0, k1 * t1, k2 * t2, acc[i0], acc[i1], acc[i2]);
+                    else Q2<double>::deriv2T_acc(f * k0 * t0, f * k1 * t1, f * k2 * t2, acc[i0], acc[i1], acc[i2]);
+                }
+        } else {
+            const double fd = sc.s[d] * sc.s[d], fe = sc.s[d] * sc.s[C];
+            const double *v = ul + d * GQ + t;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                double e[3][3]; // [position along C][along d]
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    Q2<double>::deriv2(v[qidx<C, d>(0, j, k) * BNT], v[qidx<C, d>(1, j, k) * BNT],
+                                       v[qidx<C, d>(2, j, k) * BNT], e[0][j], e[1][j], e[2][j]);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const int i0 = qidx<C, d>(i, 0, k), i1 = qidx<C, d>(i, 1, k), i2 = qidx<C, d>(i, 2, k);
+                    double t0, t1, t2;
+                    Q2<double>::deriv2(u[i0], u[i1], u[i2], t0, t1, t2);
+                    if constexpr (ISO) {
+                        t0 += e[i][0];
+                        t1 += e[i][1];
+                        t2 += e[i][2];
+                    } else {
+                        t0 = fd * t0 + fe * e[i][0];
+                        t1 = fd * t1 + fe * e[i][1];
+                        t2 = fd * t2 + fe * e[i][2];
+                    }
+                    Q2<double>::deriv2T_acc(nul[i0 * BNT + t] * t0, nul[i1 * BNT + t] * t1, nul[i2 * BNT + t] * t2,
+                                            acc[i0], acc[i1], acc[i2]);
+                }
+            }
         }
     };
-    cross(std::integral_constant<int, 0>{});
-    cross(std::integral_constant<int, 1>{});
-    cross(std::integral_constant<int, 2>{});
-    interp3T(acc);
+    dir(std::integral_constant<int, 0>{});
+    dir(std::integral_constant<int, 1>{});
+    dir(std::integral_constant<int, 2>{});
 }
 
-// One workgroup of three wavefronts per brick; wavefront c computes velocity
-// component c of every cell.  The nodal fields (phi, x and u0, three
-// components each, and with three phases the frozen temperature) are staged
-// once; each wavefront interpolates its own components of x and u0 and the
-// coefficients at a third of the Gauss points, and the brick's Gauss-point
-// fields are exchanged through LDS:
+// One workgroup of four wavefronts per brick.  Wavefronts 0-2 interpolate
+// their own components of x and u0 while wavefront 3 forms the coefficients;
+// the brick's Gauss-point fields are exchanged through LDS:
 //   region A: staging, then u0 at the Gauss points (3 fields), then x at the
-//             Gauss points (3 fields); region C: rho W and nu.
-template <int HK, bool TR, bool TP>
+//             Gauss points (3 fields); regions B and C: rho W, and the
+//             viscosity (three phases: the Darcy weight first, the viscosity,
+//             held by wavefront 3 until then, after the convection).
+// The coefficients have a wavefront of their own because the two bricks that
+// fit a CU (LDS, and 256 VGPRs) are then eight wavefronts, two on each SIMD:
+// with three wavefronts per brick that also share the coefficients, two SIMDs
+// ran two wavefronts and two ran one, and every wavefront interpolated phi.
+template <int HK, bool TR, bool TP, bool ISO>
 __global__ void __launch_bounds__(ONT) oseen_apply_kernel(KMesh m, OseenArgs a, const double *__restrict__ x,
                                                           double *__restrict__ y, double *__restrict__ face)
 {
@@ -282,29 +298,46 @@ __global__ void __launch_bounds__(ONT) oseen_apply_kernel(KMesh m, OseenArgs a, 
         br.stage_nodes_wg<ONT, 7>(m, threadIdx.x, src, dst, 0xEu);
     }
     __syncthreads();
-    double u[27], acc[27];
-    {
-        double w0[27];
-        if (comp == 0) oseen_phase1<0, HK, TP>(br, a, m, A, rwl, nul, u, w0, acc);
-        else if (comp == 1) oseen_phase1<1, HK, TP>(br, a, m, A, rwl, nul, u, w0, acc);
-        else oseen_phase1<2, HK, TP>(br, a, m, A, rwl, nul, u, w0, acc);
-        __syncthreads(); // staging no longer read: region A takes u0 at the Gauss points
+    if (comp == 3) { // the coefficients; the barriers below match those of the components
+        double nu[27];
+        oseen_coeffs<HK, TP, ISO>(br, a, m, ps, tcs, rwl, nul, nu);
+        if constexpr (!TP) {
 #pragma unroll
-        for (int q = 0; q < 27; ++q) A[comp * GQ + q * BNT + br.t] = w0[q];
+            for (int q = 0; q < 27; ++q) nul[q * BNT + br.t] = nu[q];
+        }
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+        if constexpr (TP) {
+#pragma unroll
+            for (int q = 0; q < 27; ++q) nul[q * BNT + br.t] = nu[q];
+        }
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+        return;
     }
+    double u[27], acc[27];
+    br.gather27(us + comp * NB, u);
+    interp3(u);
+    pin27(u);
+    br.gather27(u0s + comp * NB, acc);
+    interp3(acc);
+    __syncthreads(); // staging no longer read: region A takes u0 at the Gauss points
+#pragma unroll
+    for (int q = 0; q < 27; ++q) A[comp * GQ + q * BNT + br.t] = acc[q];
     __syncthreads();
-    if (comp == 0) oseen_phase2<0, TR, TP>(br, a, m, rwl, A, u, acc);
-    else if (comp == 1) oseen_phase2<1, TR, TP>(br, a, m, rwl, A, u, acc);
-    else oseen_phase2<2, TR, TP>(br, a, m, rwl, A, u, acc);
+    oseen_convection<TR, TP, ISO>(br, a, m, rwl, nul, A, u, acc);
     __syncthreads(); // u0 no longer read: region A takes x at the Gauss points
 #pragma unroll
     for (int q = 0; q < 27; ++q) A[comp * GQ + q * BNT + br.t] = u[q];
     __syncthreads();
-    if (comp == 0) oseen_phase3<0>(br, m, nul, A, u, acc);
-    else if (comp == 1) oseen_phase3<1>(br, m, nul, A, u, acc);
-    else oseen_phase3<2>(br, m, nul, A, u, acc);
+    if (comp == 0) oseen_viscosity<0, ISO>(br, m, nul, A, u, acc);
+    else if (comp == 1) oseen_viscosity<1, ISO>(br, m, nul, A, u, acc);
+    else oseen_viscosity<2, ISO>(br, m, nul, A, u, acc);
+    interp3T(acc);
     __syncthreads(); // region A no longer read: it takes the node-sum exchange
-    br.assemble27(acc, lds + comp * 9 * BNT);
+    br.assemble27(acc, lds + comp * 9 * BNT); // one barrier inside
     double *fb = face + ((int64_t)comp * n_bricks(m) + br.brick) * BFACE;
     double *yc = y + comp * nn;
     const double *xc = x + comp * nn;
@@ -339,16 +372,29 @@ hipError_t oseen_apply(const KMesh &m, const OseenArgs &a, int transpose, const 
         if (e != hipSuccess) return e;
     }
     double *fb = (double *)face;
-    const int key = (a.tc ? 4 : 0) | (a.hkind ? 2 : 0) | (transpose ? 1 : 0);
+    // equal cell edges (a cube's cells): the derivative passes without scaling
+    const bool iso = m.hx == m.hy && m.hy == m.hz;
+    const int key = (iso ? 8 : 0) | (a.tc ? 4 : 0) | (a.hkind ? 2 : 0) | (transpose ? 1 : 0);
     switch (key) {
-    case 0: oseen_apply_kernel<0, false, false><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 1: oseen_apply_kernel<0, true, false><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 2: oseen_apply_kernel<1, false, false><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 3: oseen_apply_kernel<1, true, false><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 4: oseen_apply_kernel<0, false, true><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 5: oseen_apply_kernel<0, true, true><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 6: oseen_apply_kernel<1, false, true><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
-    case 7: oseen_apply_kernel<1, true, true><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
+#define OSEEN_CASE(K, HK, TR, TP, ISO) \
+    case K: oseen_apply_kernel<HK, TR, TP, ISO><<<nb, ONT, 0, s>>>(m, a, x, y, fb); break;
+        OSEEN_CASE(0, 0, false, false, false)
+        OSEEN_CASE(1, 0, true, false, false)
+        OSEEN_CASE(2, 1, false, false, false)
+        OSEEN_CASE(3, 1, true, false, false)
+        OSEEN_CASE(4, 0, false, true, false)
+        OSEEN_CASE(5, 0, true, true, false)
+        OSEEN_CASE(6, 1, false, true, false)
+        OSEEN_CASE(7, 1, true, true, false)
+        OSEEN_CASE(8, 0, false, false, true)
+        OSEEN_CASE(9, 0, true, false, true)
+        OSEEN_CASE(10, 1, false, false, true)
+        OSEEN_CASE(11, 1, true, false, true)
+        OSEEN_CASE(12, 0, false, true, true)
+        OSEEN_CASE(13, 0, true, true, true)
+        OSEEN_CASE(14, 1, false, true, true)
+        OSEEN_CASE(15, 1, true, true, true)
+#undef OSEEN_CASE
     }
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && t && t->stop) e = hipEventRecord(t->stop, s);
