@@ -1,10 +1,8 @@
 // brick.hpp -- the cell-brick work unit shared by the operator kernels.
 //
 // A 64-thread workgroup (one wavefront) owns a brick of 4x4x4 cells, one
-// thread per cell; the brick's 9x9x9 Q2 nodes are staged in LDS.  The brick
-// code is templated on the brick's depth along z (BrickT<BZ>): the FP32
-// heat applies take 4x4x8 cells, two wavefronts per workgroup and 9x9x17
-// nodes.
+// thread per cell; the brick's 9x9x9 Q2 nodes are staged in LDS.  The heat
+// applies use the same cells and node sums in slabs (Slab, below).
 //
 // Staging is per cell (each thread reads the 27 nodes of its cell and
 // writes them to LDS; nodes shared by cells of the brick are written with
@@ -47,23 +45,15 @@ constexpr int NXCD = 8;
 // measured no faster there).
 template <typename T> __host__ __device__ constexpr int lds_row() { return sizeof(T) == 8 ? BP + 1 : BP; }
 template <typename T> __host__ __device__ constexpr int lds_plane() { return lds_row<T>() * BP; }
-// LDS entries of one staged field of a brick BZ cells deep in z
-template <typename T, int BZ = BB> __host__ __device__ constexpr int lds_field() { return lds_plane<T>() * (2 * BZ + 1); }
+// LDS entries of one staged field
+template <typename T> __host__ __device__ constexpr int lds_field() { return lds_plane<T>() * BP; }
 
-// Bricks are BB x BB x BZ cells; BZ = BB unless a kernel says otherwise.
-// Per brick: threads (cells), node planes along z, nodes, face-buffer slots.
-template <int BZ> struct BrickDims {
-    static constexpr int NT = BB * BB * BZ;
-    static constexpr int PZ = 2 * BZ + 1;
-    static constexpr int NNODES = BP * BP * PZ;
-    static constexpr int NFACE = NNODES + 2 * BP * PZ; // see face_slot
-};
-constexpr int BNB = BrickDims<BB>::NNODES;  // nodes per 4x4x4 brick
-constexpr int BFACE = BrickDims<BB>::NFACE; // its face-buffer slots
+constexpr int BNB = BP * BP * BP;            // nodes per brick
+constexpr int BFACE = BNB + 2 * BP * BP;     // its face-buffer slots, see face_slot
 
-template <int BZ = BB> __host__ __device__ inline int64_t n_bricks(const KMesh &m)
+__host__ __device__ inline int64_t n_bricks(const KMesh &m)
 {
-    return (int64_t)((m.nx + BB - 1) / BB) * ((m.ny + BB - 1) / BB) * ((m.nz + BZ - 1) / BZ);
+    return (int64_t)((m.nx + BB - 1) / BB) * ((m.ny + BB - 1) / BB) * ((m.nz + BB - 1) / BB);
 }
 
 // Face-buffer slot of a brick node (only the slots of shared surface nodes
@@ -71,15 +61,16 @@ template <int BZ = BB> __host__ __device__ inline int64_t n_bricks(const KMesh &
 // of their own, (side, ly, lz) with ly fastest, so that the combine pass
 // reads them in runs along y; every other node keeps its lexicographic brick
 // index, so that runs along x stay contiguous.
-template <int BZ = BB> __host__ __device__ __forceinline__ constexpr int face_slot(int lx, int ly, int lz)
+__host__ __device__ __forceinline__ constexpr int face_slot(int lx, int ly, int lz)
 {
-    return (lx == 0 || lx == 2 * BB) ? BrickDims<BZ>::NNODES + (lx ? BP * (2 * BZ + 1) : 0) + ly + BP * lz
+    return (lx == 0 || lx == 2 * BB) ? BNB + (lx ? BP * BP : 0) + ly + BP * lz
                                      : lx + BP * (ly + BP * lz);
 }
 
-template <int BZ> struct BrickT {
-    static constexpr int NT = BrickDims<BZ>::NT, PZ = BrickDims<BZ>::PZ;
-    static constexpr int NNODES = BrickDims<BZ>::NNODES, NFACE = BrickDims<BZ>::NFACE;
+struct Brick {
+    static constexpr int NT = BNT, PZ = BP, NNODES = BNB, NFACE = BFACE;
+    static constexpr int CX = BB; // cells along x
+    static __device__ __forceinline__ constexpr int face_slot_of(int lx, int ly, int lz) { return face_slot(lx, ly, lz); }
 
     int brick;         // natural brick index (x fastest)
     int bx, by, bz;    // brick coordinates
@@ -90,7 +81,7 @@ template <int BZ> struct BrickT {
     bool valid;
     bool lastx, lasty, lastz;
 
-    __device__ __forceinline__ BrickT(const KMesh &m, int slot) : BrickT(m, slot, xcd_index()) {}
+    __device__ __forceinline__ Brick(const KMesh &m, int slot) : Brick(m, slot, xcd_index()) {}
 
     // XCD-contiguous numbering: workgroup b runs on XCD b % 8; XCD k gets
     // the workgroup indices [start_k, start_k + count_k).
@@ -102,19 +93,20 @@ template <int BZ> struct BrickT {
     }
 
     // The brick of natural index b.
-    __device__ __forceinline__ BrickT(const KMesh &m, int slot, int b) : t(slot)
+    __device__ __forceinline__ Brick(const KMesh &m, int slot, int b) : t(slot)
     {
         brick = b;
-        const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB;
-        bx = brick % nbx;
-        by = (brick / nbx) % nby;
-        bz = brick / (nbx * nby);
+        const int nbx = (int)((unsigned)(m.nx + BB - 1) / BB), nby = (int)((unsigned)(m.ny + BB - 1) / BB);
+        const int q = (int)udiv((unsigned)brick, (unsigned)nbx, m.rbx);
+        bx = brick - q * nbx;
+        bz = (int)udiv((unsigned)q, (unsigned)nby, m.rby);
+        by = q - bz * nby;
         c0x = bx * BB;
         c0y = by * BB;
-        c0z = bz * BZ;
+        c0z = bz * BB;
         ncx = min(BB, m.nx - c0x);
         ncy = min(BB, m.ny - c0y);
-        ncz = min(BZ, m.nz - c0z);
+        ncz = min(BB, m.nz - c0z);
         tx = t & (BB - 1);
         ty = (t / BB) & (BB - 1);
         tz = t / (BB * BB);
@@ -193,7 +185,7 @@ template <int BZ> struct BrickT {
         // brick's low faces and every high node is shared.  Such bricks take
         // a copy of the visits with these flags folded in (a uniform branch;
         // 26.1 -> 25.6 us for the FP64 apply kernel at 64^3).
-        const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB, nbz = (m.nz + BZ - 1) / BZ;
+        const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB, nbz = (m.nz + BB - 1) / BB;
         const bool inner = bx > 0 && by > 0 && bz > 0 && bx < nbx - 1 && by < nby - 1 && bz < nbz - 1 &&
                            !touches_dirichlet(m);
         auto inode = [&](auto A, auto B, auto C) {
@@ -302,38 +294,6 @@ template <int BZ> struct BrickT {
                 }
     }
 
-    // Stage NF (1 or 2) nodal fields into LDS, unmasked, every read issued
-    // before the first LDS write.
-    template <int NF, typename T>
-    __device__ __forceinline__ void stage_fields(const KMesh &m, const T *__restrict__ g0, T *l0s,
-                                                 const T *__restrict__ g1, T *l1s) const
-    {
-        const __amdgpu_buffer_rsrc_t r0 = nodal_rsrc(m, g0), r1 = nodal_rsrc(m, NF == 2 ? g1 : g0);
-        const unsigned vo = stage_vo<T>(m), sy = (unsigned)sizeof(T) * (unsigned)m.NX, sz = sy * (unsigned)m.NY;
-        const int l0 = stage_l0<T>();
-        constexpr int R = lds_row<T>(), P = lds_plane<T>();
-        T v0[27], v1[27];
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-            for (int b = 0; b < 3; ++b)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const unsigned vofs = vo + (unsigned)(a * sizeof(T)), sofs = b * sy + c * sz;
-                    v0[a + 3 * b + 9 * c] = nodal_load<T>(r0, vofs, sofs);
-                    if constexpr (NF == 2) v1[a + 3 * b + 9 * c] = nodal_load<T>(r1, vofs, sofs);
-                }
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-#pragma unroll
-            for (int b = 0; b < 3; ++b)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    const int l = l0 + a + R * b + P * c;
-                    l0s[l] = v0[a + 3 * b + 9 * c];
-                    if constexpr (NF == 2) l1s[l] = v1[a + 3 * b + 9 * c];
-                }
-    }
     // Node-parallel staging over a workgroup of WG threads (tid = the
     // thread's index in it) of NF fields of 8-byte entries: field f is read
     // from src[f] into the LDS region dst[f]; with MASK, a field with bit f
@@ -421,16 +381,6 @@ template <int BZ> struct BrickT {
     {
         if (maskbits) stage_rows<WG, NF, true, double>(m, tid, src, dst, maskbits);
         else stage_rows<WG, NF, false, double>(m, tid, src, dst, 0u);
-    }
-
-    template <typename T> __device__ __forceinline__ void load_fields(const KMesh &m, const T *g0, T *l0s) const
-    {
-        stage_fields<1, T>(m, g0, l0s, nullptr, nullptr);
-    }
-    template <typename T>
-    __device__ __forceinline__ void load_fields(const KMesh &m, const T *g0, T *l0s, const T *g1, T *l1s) const
-    {
-        stage_fields<2, T>(m, g0, l0s, g1, l1s);
     }
 
     // The cell's 27 nodal values with its Dirichlet nodes read as zero (the
@@ -552,8 +502,6 @@ template <int BZ> struct BrickT {
     }
 };
 
-using Brick = BrickT<BB>;
-
 // ---------------------------------------------------------------------------
 // Shared-node combine.  The nodes that several bricks touch lie on the
 // internal brick planes of some direction.  A node's value is the sum of the
@@ -566,50 +514,45 @@ using Brick = BrickT<BB>;
 // diagonal).
 // ---------------------------------------------------------------------------
 
-// Brick-owned combine: a wavefront per 4 cells of brick depth (numbered
-// like the brick kernels, XCD-contiguously).  Each shared node is finished
+// Brick-owned combine: a wavefront per brick (numbered like the brick
+// kernels, XCD-contiguously), two per slab of four sub-bricks.  Each shared node is finished
 // by the one brick that holds it at local index 0 in every direction in
 // which it is shared: the brick's nodes on its low faces that lie on
 // internal brick planes, without its shared high faces (the next brick's
 // low faces).  For a 4x4x4 brick with lower neighbours in x, y and z that is
 // up to 64 + 56 + 49 nodes (217 for a brick at the far end of the mesh in
-// every direction), at most four per lane; a 4x4x8 brick has up to
-// 81 + 144 + 128 = 353 over two wavefronts, three per lane.  They are
+// every direction), at most four per lane; a slab has up to 297 + 264 + 64 =
+// 625 over two wavefronts, five per lane.  They are
 // enumerated in three slabs: l_z = 0 (runs along x); l_y = 0 (runs along x);
 // l_x = 0 (runs along y, where the x-face slots are contiguous).  The
 // partials are summed in the fixed order above (the same order as a pass
 // that enumerates the shared nodes flat, which this pass replaced with
 // bitwise the same results); all loads of a lane's nodes are issued before
 // the sums.
-// Lanes that finish one brick's shared nodes: a wavefront per 4 cells of
-// brick depth.
-template <int BZ> struct CombineLanes {
-    static constexpr int value = BNT * BZ / BB;
-};
-
-// The visit for one brick; INNER: a brick with neighbours on all six sides
+// The visit for one brick (or slab: BR gives the extents, CX x BB x CZ cells,
+// and the face-buffer slots); INNER: a brick with neighbours on all six sides
 // and no Dirichlet face, for which the ranges, the sharing flags and the
-// slab divisions are compile-time constants and nothing is constrained.
-template <typename T, bool SKIP_CONSTRAINED, int BZ, bool INNER, typename F>
-__device__ __forceinline__ void combine_brick_nodes(const KMesh &m, const BrickT<BZ> &br, int nbx, int nby, int nbz,
+// divisions are compile-time constants and nothing is constrained.  L lanes
+// finish one brick.
+template <typename T, bool SKIP_CONSTRAINED, int L, bool INNER, typename BR, typename F>
+__device__ __forceinline__ void combine_brick_nodes(const KMesh &m, const BR &br, int nbx, int nby, int nbz,
                                                     int lane, const T *__restrict__ face, F f)
 {
-    using BD = BrickDims<BZ>;
+    constexpr int BX = BR::CX;
     // lower neighbour: the low face is shared
     const bool fx = INNER || br.bx > 0, fy = INNER || br.by > 0, fz = INNER || br.bz > 0;
     // local range without a shared high face
-    const int ex = INNER ? 2 * BB : 2 * br.ncx + (br.bx == nbx - 1 ? 1 : 0);
+    const int ex = INNER ? 2 * BX : 2 * br.ncx + (br.bx == nbx - 1 ? 1 : 0);
     const int ey = INNER ? 2 * BB : 2 * br.ncy + (br.by == nby - 1 ? 1 : 0);
-    const int ez = INNER ? 2 * BZ : 2 * br.ncz + (br.bz == nbz - 1 ? 1 : 0);
+    const int ez = INNER ? 2 * BB : 2 * br.ncz + (br.bz == nbz - 1 ? 1 : 0);
     const int z0 = fz ? 1 : 0, y0 = fy ? 1 : 0;
     const int nzs = fz ? ex * ey : 0, nys = fy ? ex * (ez - z0) : 0, nxs = fx ? (ey - y0) * (ez - z0) : 0;
     const int tot = nzs + nys + nxs;
-    // small exact divisions: floor((j + 1/2) / w) for j < 512, w <= 9
+    // small exact divisions: floor((j + 1/2) / w) for j < 1024, w <= 33
     const float iex = 1.0f / (float)ex, iw = 1.0f / (float)(ey - y0);
     auto div = [&](int j, int w, float iw_) { return INNER ? j / w : (int)(((float)j + 0.5f) * iw_); };
-    // nodes per lane: BP^2 + 2 BP (PZ - 1) at most over the brick's lanes
-    constexpr int L = CombineLanes<BZ>::value;
-    constexpr int K = (BP * BP + 2 * BP * (BD::PZ - 1) + L - 1) / L;
+    // nodes per lane: a z, a y and an x face at most over the brick's lanes
+    constexpr int K = ((2 * BX + 1) * BP + (2 * BX + 1) * 2 * BB + 2 * BB * 2 * BB + L - 1) / L;
     bool has[K], con[K];
     int64_t g[K];
     T v[K][8];
@@ -637,16 +580,16 @@ __device__ __forceinline__ void combine_brick_nodes(const KMesh &m, const BrickT
         g[k] = node_index(m, gx, gy, gz);
         const bool read = has[k] && !(SKIP_CONSTRAINED && con[k]);
         const bool sx = lx == 0 && fx, sy = ly == 0 && fy, sz = lz == 0 && fz;
-        const int kx0 = sx ? br.bx - 1 : br.bx, lx0 = sx ? 2 * BB : lx;
+        const int kx0 = sx ? br.bx - 1 : br.bx, lx0 = sx ? 2 * BX : lx;
         const int ky0 = sy ? br.by - 1 : br.by, ly0 = sy ? 2 * BB : ly;
-        const int kz0 = sz ? br.bz - 1 : br.bz, lz0 = sz ? 2 * BZ : lz;
+        const int kz0 = sz ? br.bz - 1 : br.bz, lz0 = sz ? 2 * BB : lz;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int ex_ = e & 1, ey_ = (e >> 1) & 1, ez_ = e >> 2;
             v[k][e] = T(0);
             if (read && (!ex_ || sx) && (!ey_ || sy) && (!ez_ || sz)) {
                 const int b = (kx0 + ex_) + nbx * ((ky0 + ey_) + nby * (kz0 + ez_));
-                v[k][e] = face[(int64_t)b * BD::NFACE + face_slot<BZ>(ex_ ? 0 : lx0, ey_ ? 0 : ly0, ez_ ? 0 : lz0)];
+                v[k][e] = face[(int64_t)b * BR::NFACE + BR::face_slot_of(ex_ ? 0 : lx0, ey_ ? 0 : ly0, ez_ ? 0 : lz0)];
             }
         }
     }
@@ -660,30 +603,439 @@ __device__ __forceinline__ void combine_brick_nodes(const KMesh &m, const BrickT
     }
 }
 
-template <typename T, bool SKIP_CONSTRAINED, int BZ = BB, typename F>
+template <typename T, bool SKIP_CONSTRAINED, typename F>
 __device__ __forceinline__ void combine_brick_visit(const KMesh &m, int brick, int lane, const T *__restrict__ face,
                                                     F f)
 {
-    const BrickT<BZ> br(m, lane, brick);
-    const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB, nbz = (m.nz + BZ - 1) / BZ;
+    const Brick br(m, lane, brick);
+    const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB, nbz = (m.nz + BB - 1) / BB;
     const bool inner = br.bx > 0 && br.by > 0 && br.bz > 0 && br.bx < nbx - 1 && br.by < nby - 1 &&
                        br.bz < nbz - 1 && !br.touches_dirichlet(m);
-    if (inner) combine_brick_nodes<T, SKIP_CONSTRAINED, BZ, true>(m, br, nbx, nby, nbz, lane, face, f);
-    else combine_brick_nodes<T, SKIP_CONSTRAINED, BZ, false>(m, br, nbx, nby, nbz, lane, face, f);
+    constexpr int L = BNT; // a wavefront per brick
+    if (inner) combine_brick_nodes<T, SKIP_CONSTRAINED, L, true>(m, br, nbx, nby, nbz, lane, face, f);
+    else combine_brick_nodes<T, SKIP_CONSTRAINED, L, false>(m, br, nbx, nby, nbz, lane, face, f);
 }
 
-// Threads of a brick-combine workgroup: 4 bricks of 4x4x4 cells, 2 of 4x4x8.
+// ---------------------------------------------------------------------------
+// Slabs.  A workgroup of W wavefronts owns 4W x 4 x 4 cells, W 4x4x4
+// sub-bricks side by side along x, one per wavefront, over (8W + 1) x 9 x 9
+// nodes staged once in LDS.  The cells are computed as in a brick; what
+// changes is how the nodes travel: staged and finished row by row by the
+// whole workgroup, the node sums passing through LDS, with a few bit tests
+// per row where a brick visits its owned nodes cell by cell, 27 divergent
+// groups (a wavefront alone on its CU spent 4200 of its 13700 cycles there,
+// 7000 on a brick at the boundary of the mesh).
+// W = 4: a brick's rows are 9 nodes, 72 or 36 bytes of a 128-byte line; on
+// 128^3 cells in FP32 the brick kernel made 9.7M L2 reads and 8.4M L2 writes
+// for 1.7M lines and kept the address units busy 79 % of the time, and a
+// workgroup waited 33000 of its 48000 cycles for its staging reads (11800 of
+// 25500 now).  A slab's rows are 33 nodes; it shares three quarters of the
+// nodes that four bricks share with their neighbours, and a quarter of those
+// on planes across x, which the combine pass can only write one by one.
+// W = 1 spreads a small mesh over four times the CUs.
+// ---------------------------------------------------------------------------
+
+// A visitor whose arrays must stay in registers has to be inlined.
+#define MF_INLINE __attribute__((always_inline))
+
+// f(0), f(1), ... with the index a compile-time constant (a loop over an
+// array in registers that the optimizer might split instead of unrolling).
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
+
+__host__ __device__ inline unsigned ceil_div(int n, int d) { return (unsigned)(n + d - 1) / (unsigned)d; }
+template <int W> __host__ __device__ inline int64_t n_slabs(const KMesh &m)
+{
+    return (int64_t)ceil_div(m.nx, W * BB) * ceil_div(m.ny, BB) * ceil_div(m.nz, BB);
+}
+
+// Slabs of four sub-bricks: where at least three of four sub-brick slots along
+// x hold cells (then their face buffer, 2673 slots, is no larger than the
+// 3 * 891 of as many bricks either), and from 1200 bricks on, where the four
+// wavefronts of a slab no longer leave CUs idle.  FP64 apply, W = 4 against
+// W = 1: 32^3 cells (512 bricks) 14.4 / 13.6 us, 40^3 17.7 / 16.0, 44^3 (1331)
+// 18.4 / 18.7, 48^3 19.2 / 20.2, 64^3 30.2 / 35.0, 112^3 136 / 183; with
+// sub-bricks left over: 53^3 (14 of 16) 26.8 / 25.4, 67^3 (17 of 20) 37.9 /
+// 44.8.  FP32: 40^3 15.9 / 14.8, 48^3 17.4 / 18.0, 128^3 127 / 169.
+// The heavier forms (a third staged field, coefficients per point, the sine
+// Heaviside, whose polynomial only some wavefronts of a slab evaluate) pay
+// more for a partly filled last round of slabs: convective transpose
+// 45x64x51 (624 slabs on 512 places) 35.4 / 33.8 us, 64^3 49.3 / 54.0;
+// coefficients per point FP32 48^3 19.0 / 18.0; sine 50x37x61 27.6 / 24.7,
+// 64^3 36.6 / 36.1.
+inline bool use_wide_slabs(const KMesh &m, bool heavy)
+{
+    return n_bricks(m) >= (heavy ? 3600 : 1200) && (int)ceil_div(m.nx, BB) >= 3 * (int)ceil_div(m.nx, 4 * BB);
+}
+
+// LDS of W > 1 beside the staged fields: the sums on the sub-bricks' x-high
+// faces (81 each; read in whole steps of rows, hence the padding).
+template <int W> __host__ __device__ constexpr int slab_xhi() { return W > 1 ? 81 * (W - 1) + 8 : 0; }
+
+template <int W_, int R_ = (W_ == 1 ? 10 : 8 * W_ + 4)> struct Slab {
+    static constexpr int W = W_, NT = W * BNT;
+    static constexpr int RX = 2 * W * BB, SP = RX + 1; // nodes along x without and with the high face
+    static constexpr int CX = W * BB;
+    static constexpr int NFACE = SP * BP * BP; // one slot per node, surface nodes used
+    static __device__ __forceinline__ constexpr int face_slot_of(int lx, int ly, int lz)
+    {
+        return lx + SP * (ly + BP * lz);
+    }
+    // LDS layout of a staged field: node (lx, ly, lz) at lx + R ly + plane lz.
+    // A wavefront gathers nodes (2tx + a, 2ty + b, 2tz + c): with R = 4 (mod
+    // 16) the 16 lanes of a z plane fall on 16 different 8-byte banks; the
+    // FP32 planes are padded so that two z planes of lanes do not meet.  W = 1
+    // keeps rows of 10: with 12 three staged fields would leave six
+    // workgroups per CU instead of eight.
+    static constexpr int R = R_;
+    static_assert(R >= SP, "a padding slot in row 0 takes the writes of idle threads");
+    template <typename T> static __host__ __device__ constexpr int plane()
+    {
+        return sizeof(T) == 8 ? R * BP : (R * BP + 15) / 32 * 32 + 16;
+    }
+    template <typename T> static __host__ __device__ constexpr int field() { return plane<T>() * BP; }
+
+    int brick;         // natural slab index (x fastest)
+    int bx, by, bz;    // slab coordinates
+    int c0x, c0y, c0z; // first cell
+    int ncx, ncy, ncz; // valid cells per direction
+    int tid, w, t;     // thread, wavefront (uniform), lane
+    int tx, ty, tz;    // cell within the wavefront's sub-brick
+    bool valid;
+
+    __device__ __forceinline__ Slab(const KMesh &m, int tid_) : Slab(m, tid_, Brick::xcd_index()) {}
+    __device__ __forceinline__ Slab(const KMesh &m, int tid_, int b) : brick(b), tid(tid_)
+    {
+        const int nbx = (int)ceil_div(m.nx, CX), nby = (int)ceil_div(m.ny, BB);
+        const int q = (int)udiv((unsigned)brick, (unsigned)nbx, W == 1 ? m.rbx : m.rsx);
+        bx = brick - q * nbx;
+        bz = (int)udiv((unsigned)q, (unsigned)nby, m.rby);
+        by = q - bz * nby;
+        c0x = bx * CX;
+        c0y = by * BB;
+        c0z = bz * BB;
+        ncx = min(CX, m.nx - c0x);
+        ncy = min(BB, m.ny - c0y);
+        ncz = min(BB, m.nz - c0z);
+        w = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / BNT);
+        t = tid % BNT;
+        tx = t & (BB - 1);
+        ty = (t / BB) & (BB - 1);
+        tz = t / (BB * BB);
+        valid = w * BB + tx < ncx && ty < ncy && tz < ncz;
+    }
+    __device__ __forceinline__ int64_t cell_index(const KMesh &m) const
+    {
+        return (int64_t)(c0x + w * BB + tx) + (int64_t)m.nx * ((c0y + ty) + (int64_t)m.ny * (c0z + tz));
+    }
+    // The slab's faces as bits (x low, x high, y low, ...): those shared with
+    // a neighbouring slab, and those on a Dirichlet face of the mesh.
+    __device__ __forceinline__ unsigned shared_faces(const KMesh &m) const
+    {
+        return (bx > 0 ? 1u : 0u) | (c0x + CX < m.nx ? 2u : 0u) | (by > 0 ? 4u : 0u) | (c0y + BB < m.ny ? 8u : 0u) |
+               (bz > 0 ? 16u : 0u) | (c0z + BB < m.nz ? 32u : 0u);
+    }
+    __device__ __forceinline__ unsigned dirichlet_faces(const KMesh &m) const { return m.dirichlet & ~shared_faces(m); }
+    // Neighbours on all six sides (and so no Dirichlet face).
+    __device__ __forceinline__ bool inner(const KMesh &m) const { return shared_faces(m) == 63u; }
+    // The faces on which local node (lx, ly, lz) lies.
+    __device__ __forceinline__ unsigned x_faces(int lx) const { return (lx == 0 ? 1u : 0u) | (lx == 2 * ncx ? 2u : 0u); }
+    __device__ __forceinline__ unsigned yz_faces(int ly, int lz) const
+    {
+        return (ly == 0 ? 4u : 0u) | (ly == 2 * ncy ? 8u : 0u) | (lz == 0 ? 16u : 0u) | (lz == 2 * ncz ? 32u : 0u);
+    }
+
+    // Visit the slab's nodes with lx < 8W, eight rows per step: thread tid takes
+    // node lx = tid mod 8W of the rows r0 + 8 k, r0 = tid / 8W, row = ly + 9 lz.
+    // Since a plane has one row more than a step, ly = r0 - k (+ 9) and
+    // lz = k (- 1): everything is a constant step per k and one comparison,
+    // and the rows on a slab face are known per step (see the finishing
+    // pass).  f(k, slot, off, ly, lz, ok) with k a constant, slot the node in a
+    // staged field of T, off its element offset from the slab's first node in
+    // a nodal array; ok is false only beyond the last row (last step).
+    static constexpr int RPS = NT / RX, STEPS = (BP * BP + RPS - 1) / RPS;
+    static_assert(RPS == BP - 1 && STEPS == 11, "the row arithmetic of for_rows");
+    template <typename T, typename F> __device__ __forceinline__ void for_rows(const KMesh &m, F f) const
+    {
+        int i = tid;
+        asm volatile("" : "+v"(i)); // set up per call: nothing kept live across visits
+        const int lx = i % RX, r0 = i / RX;
+        constexpr int P = plane<T>();
+        const int slot0 = lx + R * r0;
+        const unsigned off0 = (unsigned)lx + (unsigned)m.NX * (unsigned)r0;
+        const unsigned S = (unsigned)m.NX * ((unsigned)m.NY - 1u), C = (unsigned)m.NX * (BP - (unsigned)m.NY);
+        static_for<STEPS>([&](auto kc) MF_INLINE {
+            constexpr int k = decltype(kc)::value;
+            if constexpr (k < STEPS - 1) {
+                const bool lo = r0 < k; // the row lies in plane k - 1
+                f(kc, slot0 + (P - R) * k + (lo ? R * BP - P : 0), off0 + k * S + (lo ? C : 0u), r0 - k + (lo ? BP : 0),
+                  k - (lo ? 1 : 0), true);
+            } else { // row 80 (thread row 0), the last one
+                f(kc, lx + R * (BP - 1) + P * (BP - 1), (unsigned)lx + (unsigned)m.NX * ((BP - 1) + (unsigned)m.NY * (BP - 1)),
+                  BP - 1, BP - 1, r0 == 0);
+            }
+        });
+    }
+    // The same for the nodes lx = 8W: 81 of them, f(k, ...) for row tid + NT k.
+    static constexpr int ESTEPS = (BP * BP + NT - 1) / NT;
+    template <typename T, typename F> __device__ __forceinline__ void for_edge(const KMesh &m, F f) const
+    {
+        int i = tid;
+        asm volatile("" : "+v"(i));
+        static_for<ESTEPS>([&](auto kc) MF_INLINE {
+            constexpr int k = decltype(kc)::value;
+            const int row = i + NT * k, lz = row / BP, ly = row - lz * BP;
+            f(kc, RX + R * ly + plane<T>() * lz, (unsigned)RX + (unsigned)m.NX * ((unsigned)ly + (unsigned)m.NY * lz), ly,
+              lz, row < BP * BP);
+        });
+    }
+    static constexpr int NV = STEPS + ESTEPS; // visited nodes per thread
+
+    // Stage NF nodal fields; every read is issued before the first LDS write.
+    // Rows are read from the slab's first node through a buffer resource (as
+    // Brick::stage_rows): reads beyond a clipped slab stay inside the array
+    // or past its end, where they return zero, and no valid cell uses them.
+    template <int NF, typename T>
+    __device__ __forceinline__ void stage(const KMesh &m, const T *const (&src)[NF], T *const (&dst)[NF]) const
+    {
+        __amdgpu_buffer_rsrc_t rs[NF];
+        const int64_t o = node_index(m, 2 * c0x, 2 * c0y, 2 * c0z);
+        const int64_t rem = ((int64_t)m.NX * m.NY * m.NZ - o) * (int64_t)sizeof(T);
+        const int nrec = (int)(unsigned)(rem > 0xFFFFFFFFll ? 0xFFFFFFFFll : rem);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) rs[f] = __builtin_amdgcn_make_buffer_rsrc((void *)(src[f] + o), 0, nrec, 0x00020000);
+        T v[NV][NF];
+        int at[NV];
+        auto node = [&](int k, int slot, unsigned off, bool ok) MF_INLINE {
+            at[k] = ok ? slot : SP; // idle threads write to the padding slot of row 0
+            const unsigned vofs = ok ? (unsigned)sizeof(T) * off : 0u;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[k][f] = Brick::nodal_load<T>(rs[f], vofs, 0);
+        };
+        for_rows<T>(m, [&](auto k, int slot, unsigned off, int, int, bool ok) MF_INLINE { node(k, slot, off, ok); });
+        for_edge<T>(m, [&](auto k, int slot, unsigned off, int, int, bool ok) MF_INLINE { node(STEPS + k, slot, off, ok); });
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) dst[f][at[k]] = v[k][f];
+    }
+
+    // The node sums at the visited nodes (from v[STEPS] on: the edge), all read
+    // together: the node array, plus the left sub-brick's part on the planes
+    // between sub-bricks (whose threads are the same in every step).
+    template <typename T>
+    __device__ __forceinline__ void node_values(const KMesh &m, const T *nod, const T *xhi, T (&v)[NV]) const
+    {
+        read_nodes(m, nod, v);
+        if constexpr (W == 1) return;
+        const int lx = tid % RX;
+        if ((lx & 7) == 0 && lx > 0 && lx < 2 * ncx) {
+            const T *h = xhi + 81 * ((lx >> 3) - 1) + tid / RX; // row = ly + 9 lz
+            T s[STEPS];
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k) s[k] = h[RPS * k]; // rows beyond the last one: padding
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k) v[k] += s[k];
+        }
+    }
+    // A staged field at the visited nodes.
+    template <typename T> __device__ __forceinline__ void read_nodes(const KMesh &m, const T *f, T (&v)[NV]) const
+    {
+        for_rows<T>(m, [&](auto k, int slot, unsigned, int, int, bool) MF_INLINE { v[k] = f[slot]; });
+        for_edge<T>(m, [&](auto k, int slot, unsigned, int, int, bool ok) MF_INLINE { v[STEPS + k] = f[ok ? slot : 0]; });
+    }
+
+    template <typename T> __device__ __forceinline__ int cell_slot() const
+    {
+        return valid ? 2 * (w * BB + tx) + R * 2 * ty + plane<T>() * 2 * tz : 0;
+    }
+    // The cell's 27 nodal values from LDS.
+    template <typename T> __device__ __forceinline__ void gather27(const T *lds, T *v) const
+    {
+        const T *p = lds + cell_slot<T>();
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) v[a + 3 * b + 9 * c] = p[a + R * b + plane<T>() * c];
+    }
+    // The same with the cell's Dirichlet nodes read as zero.
+    template <typename T> __device__ __forceinline__ void gather27_dirichlet(const KMesh &m, const T *lds, T *v) const
+    {
+        gather27(lds, v);
+        const unsigned f6 = dirichlet_faces(m);
+        if (f6 == 0u) return;
+        const int lx = 2 * (w * BB + tx);
+        const unsigned lo = (x_faces(lx) | yz_faces(2 * ty, 2 * tz)) & f6;
+        const unsigned hi = (x_faces(lx + 2) | yz_faces(2 * ty + 2, 2 * tz + 2)) & f6;
+        const bool dx0 = lo & 1u, dx2 = hi & 2u, dy0 = lo & 4u, dy2 = hi & 8u, dz0 = lo & 16u, dz2 = hi & 32u;
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const bool k = (a == 0 && dx0) || (a == 2 && dx2) || (b == 0 && dy0) || (b == 2 && dy2) ||
+                                   (c == 0 && dz0) || (c == 2 && dz2);
+                    v[a + 3 * b + 9 * c] = k ? T(0) : v[a + 3 * b + 9 * c];
+                }
+    }
+
+    // Node sums of the wavefront's sub-brick (as Brick::assemble27, within
+    // the wavefront) written to the node array nod (layout of a staged field).
+    // xch: the wavefront's own 9 x 64 values (with W = 1 it may overlay nod:
+    // it is read before the sums are written).  Every cell writes all its 27
+    // entries, the ones of index 2 first: where another cell of the
+    // sub-brick owns that node, its sum is written later by the same
+    // wavefront and stays (LDS operations of a wavefront are executed in
+    // order), so no write is masked.  Only the sub-brick's x-high face, which
+    // the next sub-brick's wavefront writes, goes to xhi (81 values per
+    // sub-brick but the last, added when the nodes are read).
+    template <typename T> __device__ __forceinline__ void assemble(T *u, T *xch, T *nod, T *xhi) const
+    {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const T nb = Brick::row_shr<1>(u[2 + 3 * i]);
+            u[3 * i] += tx > 0 ? nb : T(0);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) u[a + 9 * c] += Brick::row_shr<4>(u[a + 6 + 9 * c]);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) xch[i * BNT + t] = u[18 + i];
+        wave_lds_fence();
+        const int src = tz > 0 ? t - BB * BB : t;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const T nb = xch[i * BNT + src];
+            u[i] += tz > 0 ? nb : T(0);
+        }
+        if (!valid) return;
+        // x-high face entries of the sub-brick's last cells: beside the node array
+        const bool side = W > 1 && tx == BB - 1 && w * BB + BB < ncx;
+        T *const p = nod + cell_slot<T>();
+        T *const px = side ? xhi + 81 * w + 2 * ty + BP * 2 * tz : p + 2;
+        const int sy = side ? 1 : R, sz = side ? BP : plane<T>();
+#pragma unroll
+        for (int c = 2; c >= 0; --c)
+#pragma unroll
+            for (int b = 2; b >= 0; --b) {
+                px[sy * b + sz * c] = u[2 + 3 * b + 9 * c];
+                wave_lds_order();
+                p[1 + R * b + plane<T>() * c] = u[1 + 3 * b + 9 * c];
+                p[R * b + plane<T>() * c] = u[3 * b + 9 * c];
+                wave_lds_order();
+            }
+    }
+    // LDS written by this wavefront is read by its other lanes.
+    static __device__ __forceinline__ void wave_lds_fence()
+    {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    // Keeps the program order of LDS writes to the same address by different lanes.
+    static __device__ __forceinline__ void wave_lds_order()
+    {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+    }
+};
+
+// Finish the nodes of a slab: v holds the node sums (node_values), xv the
+// vector x at the nodes (only read on Dirichlet nodes, and for the energy).
+// Complete nodes go to y, shared ones to the slab's face-buffer slots;
+// Dirichlet rows get y_i = x_i.  With CG, energy gains x_i times the slab's
+// partial sum, and x_i^2 for a Dirichlet node counted once, by the slab that
+// finishes it.
+template <typename T, bool CG, typename SL>
+__device__ __forceinline__ void finish_nodes(const KMesh &m, const SL &br, T *__restrict__ y, T *__restrict__ face,
+                                             T (&v)[SL::NV], T (&xv)[SL::NV], double &energy)
+{
+    constexpr int K = SL::STEPS, SP = SL::SP;
+    T *const yb = y + node_index(m, 2 * br.c0x, 2 * br.c0y, 2 * br.c0z);
+    T *const fb = face + (int64_t)br.brick * SL::NFACE; // slot lx + SP row
+    const int lx = br.tid % SL::RX, r0 = br.tid / SL::RX;
+    T *const f0 = fb + lx + SP * r0, *const fe = fb + SL::RX + SP * br.tid;
+    const unsigned shf = br.shared_faces(m), dirf = br.dirichlet_faces(m);
+    if (shf == 63u) { // neighbours on all sides
+        // steps 0, 9 and 10 are the two z faces; of step k in between the
+        // rows r0 = k (ly = 0) and k - 1 (ly = 8) lie on the y faces
+        br.template for_rows<T>(m, [&](auto kc, int, unsigned off, int, int, bool ok) MF_INLINE {
+            constexpr int k = decltype(kc)::value;
+            T *d = f0 + k * (SL::RPS * SP);
+            if constexpr (k >= 1 && k <= 8) d = (lx == 0 || r0 == k || r0 == k - 1) ? d : yb + off;
+            if constexpr (CG) energy += ok ? (double)xv[k] * (double)v[k] : 0.0;
+            if (k < K - 1 || ok) *d = v[k];
+        });
+        br.template for_edge<T>(m, [&](auto kc, int, unsigned, int, int, bool ok) MF_INLINE {
+            constexpr int k = decltype(kc)::value;
+            if constexpr (CG) energy += ok ? (double)xv[K + k] * (double)v[K + k] : 0.0;
+            if (ok) fe[k * (SL::NT * SP)] = v[K + k];
+        });
+        return;
+    }
+    // per node the faces it lies on, tested against the slab's shared and
+    // Dirichlet faces (uniform masks)
+    const int ex = 2 * br.ncx, ey = 2 * br.ncy, ez = 2 * br.ncz;
+    auto finish = [&](T vk, T xk, T *fslot, unsigned off, unsigned fx, bool okx, int ly, int lz, bool ok) MF_INLINE {
+        ok = ok && okx && ly <= ey && lz <= ez;
+        const unsigned on = fx | br.yz_faces(ly, lz);
+        const bool sh = (on & shf) != 0u, con = (on & dirf) != 0u;
+        if constexpr (CG) {
+            const double e = con ? ((on & shf & 42u) ? 0.0 : (double)xk * (double)xk) : (double)xk * (double)vk;
+            energy += ok ? e : 0.0;
+        }
+        T *d = sh ? fslot : yb + off;
+        if (ok) *d = con ? xk : vk;
+    };
+    const unsigned fx = br.x_faces(lx), fxe = br.x_faces(SL::RX);
+    br.template for_rows<T>(m, [&](auto kc, int, unsigned off, int ly, int lz, bool ok) MF_INLINE {
+        constexpr int k = decltype(kc)::value;
+        finish(T(v[k]), T(xv[k]), f0 + k * (SL::RPS * SP), off, fx, lx <= ex, ly, lz, ok);
+    });
+    br.template for_edge<T>(m, [&](auto kc, int, unsigned off, int ly, int lz, bool ok) MF_INLINE {
+        constexpr int k = decltype(kc)::value;
+        finish(T(v[K + k]), T(xv[K + k]), fe + k * (SL::NT * SP), off, fxe, SL::RX <= ex, ly, lz, ok);
+    });
+}
+
+// Lanes that finish one slab's shared nodes, at most five nodes each.
+template <int W> __host__ __device__ constexpr int combine_lanes() { return W == 1 ? BNT : 2 * BNT; }
+constexpr int SCT = 256; // threads of a slab-combine workgroup
+
+// The combine pass of an apply on slabs: y = x on Dirichlet nodes.
+template <typename T, int W>
+__device__ __forceinline__ void combine_slabs(const KMesh &m, const T *__restrict__ face, const T *__restrict__ x,
+                                              T *__restrict__ y)
+{
+    constexpr int L = combine_lanes<W>(), PER = SCT / L;
+    const int slab = Brick::xcd_index() * PER + (int)threadIdx.x / L, lane = (int)threadIdx.x % L;
+    if (slab >= n_slabs<W>(m)) return; // whole wavefronts; no barrier follows in them
+    const Slab<W> br(m, lane, slab);
+    const int nbx = (int)ceil_div(m.nx, br.CX), nby = (int)ceil_div(m.ny, BB), nbz = (int)ceil_div(m.nz, BB);
+    auto f = [&](int64_t g, bool constrained, T s) { y[g] = constrained ? x[g] : s; };
+    if (br.inner(m)) combine_brick_nodes<T, true, L, true>(m, br, nbx, nby, nbz, lane, face, f);
+    else combine_brick_nodes<T, true, L, false>(m, br, nbx, nby, nbz, lane, face, f);
+}
+
+// Bricks (wavefronts) per brick-combine workgroup.
 constexpr int CBW = 4;
 
-template <typename T, int DMODE, int BZ = BB>
+template <typename T, int DMODE>
 __device__ __forceinline__ void combine_brick(const KMesh &m, const T *__restrict__ face, const T *__restrict__ x,
                                               T *__restrict__ y)
 {
-    constexpr int L = CombineLanes<BZ>::value, BPW = BNT * CBW / L; // bricks per workgroup
-    const int brick = Brick::xcd_index() * BPW + (int)threadIdx.x / L;
-    if (brick >= n_bricks<BZ>(m)) return; // whole wavefronts; no barrier follows in them
-    combine_brick_visit<T, DMODE != 0, BZ>(m, brick, (int)threadIdx.x % L, face,
-                                           [&](int64_t g, bool constrained, T s) {
+    const int brick = Brick::xcd_index() * CBW + (int)threadIdx.x / BNT;
+    if (brick >= n_bricks(m)) return; // whole wavefronts; no barrier follows in them
+    combine_brick_visit<T, DMODE != 0>(m, brick, (int)threadIdx.x % BNT, face, [&](int64_t g, bool constrained, T s) {
         if (DMODE != 0 && constrained) y[g] = DMODE == 1 ? x[g] : ((DMODE == 2 || DMODE == 4) ? T(1) : T(0));
         else y[g] = DMODE == 4 ? T(1) / s : s;
     });

@@ -9,12 +9,10 @@
 // (FP64, level-set coefficients); its transpose moves the derivative onto
 // the test function: alpha_c rc_q x_q u_q . grad N_i.
 //
-// Work decomposition (brick.hpp): one 64-thread workgroup (one wavefront)
-// per brick of 4x4x4 cells, one thread per cell (the FP32 applies: bricks
-// of 4x4x8 cells, two wavefronts).
-//   1. the brick's nodal x and phi are staged in LDS (FP64: each node read
-//      once, node-parallel over the wavefront; FP32: each cell reads its 27
-//      nodes); Dirichlet columns read as zero when x is gathered;
+// Work decomposition of the applies (brick.hpp): workgroups of one or four
+// wavefronts, each a brick of 4x4x4 cells, one thread per cell.
+//   1. the workgroup's nodal x and phi are staged in LDS row by row, each
+//      node read once; Dirichlet columns read as zero when x is gathered;
 //   2. each thread evaluates its cell entirely in registers by sum
 //      factorization (3x3 contractions along one direction at a time,
 //      collocation derivatives at the Gauss points, one 3-point line at a
@@ -22,10 +20,10 @@
 //   3. each owned node sums the (at most 8) cells of the brick that share it
 //      in a fixed order, in registers (cross-lane shifts in x and y, an LDS
 //      exchange in z);
-//   4. nodes complete within the brick are stored; nodes on a face shared
-//      with a neighbouring brick go to a face buffer, and a second kernel
-//      adds the partials of the bricks sharing each such node in a fixed
-//      order, brick by brick.  Every output entry is written once, without
+//   4. the node sums pass through LDS; nodes complete within the workgroup
+//      are stored; nodes on a face shared with a neighbour go to a face
+//      buffer, and a second kernel adds the partials sharing each such node
+//      in a fixed order, brick by brick.  Every output entry is written once, without
 //      atomics, and the result is bitwise reproducible.  Dirichlet nodes get
 //      y_i = x_i.
 #include <hip/hip_ext.h>
@@ -115,29 +113,21 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
         dir(std::integral_constant<int, 1>{});
         dir(std::integral_constant<int, 2>{});
     }
-    // |grad phi| H' in place of |grad phi|^2, then H in place of phi
-    if (a.penalty != 0.0) {
+    if constexpr (HK == 1) {
+        // |grad phi| H' in place of |grad phi|^2, then H in place of phi
+        if (a.penalty != 0.0) {
 #pragma unroll
-        for (int q = 0; q < 27; q += 9) {
-            double dH[9];
-            if constexpr (HK == 1) {
+            for (int q = 0; q < 27; q += 9) {
+                double dH[9];
                 heaviside_sine_derivative<9, 9>(ph + q, dH);
-            } else {
 #pragma unroll
-                for (int j = 0; j < 9; ++j) dH[j] = heaviside_linear_derivative(ph[q + j]);
-            }
-#pragma unroll
-            for (int j = 0; j < 9; ++j) {
-                gn[q + j] = dH[j] * sqrt(gn[q + j]);
-                asm volatile("" : "+v"(gn[q + j])); // one group at a time
+                for (int j = 0; j < 9; ++j) {
+                    gn[q + j] = dH[j] * sqrt(gn[q + j]);
+                    asm volatile("" : "+v"(gn[q + j])); // one group at a time
+                }
             }
         }
-    }
-    if constexpr (HK == 1) {
         heaviside_sine<27, 9>(ph);
-    } else {
-#pragma unroll
-        for (int q = 0; q < 27; ++q) ph[q] = heaviside_linear<double>(ph[q]);
     }
     if (a.tc) {
         br.gather27(ts, Tq);
@@ -149,7 +139,8 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
     const double ak_r2 = a.ak * ck_scale / (kR * kR); // ck_scale: 1, or 1/(4 h^2) for the equal-edge form
 #pragma unroll
     for (int q = 0; q < 27; ++q) {
-        const double H = ph[q];
+        const double H = HK == 1 ? ph[q] : heaviside_linear<double>(ph[q]);
+        const double gH = HK == 1 ? gn[q] : heaviside_linear_derivative(ph[q]) * sqrt(gn[q]);
         double Hs = 0.0;
         if (a.tc) {
             const double fs = fmin(fmax((a.T_liq - Tq[q]) * inv_range, 0.0), 1.0);
@@ -157,12 +148,20 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
         }
         const double k = H * (Hs * a.k_s + (1.0 - Hs) * a.k_l) + (1.0 - H) * a.k_g;
         const double rc = H * (Hs * a.rc_s + (1.0 - Hs) * a.rc_l) + (1.0 - H) * a.rc_g;
-        const double react = a.penalty * gn[q] * (a.rc_g + H * (a.rc_l - a.rc_g)) * c_rcp;
+        const double react = a.penalty * gH * (a.rc_g + H * (a.rc_l - a.rc_g)) * c_rcp;
         const double w = vol * Q2<double>::weight(q % 3) * Q2<double>::weight((q / 3) % 3) * Q2<double>::weight(q / 9);
         cm[q] = w * (a.am * rc + react);
         ck[q] = w * ak_r2 * k;
         asm volatile("" : "+v"(cm[q]), "+v"(ck[q])); // one point at a time
     }
+}
+
+// Sum over the wavefront, identical in every lane.
+__device__ __forceinline__ double wave_total(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    return __shfl(v, 0, 64);
 }
 
 // y_e = A_e x_e on one cell, in place on u (27 nodal values in, 27 out).
@@ -222,8 +221,8 @@ struct ClassCoef {
 };
 
 // H(phi) at the Gauss points of this thread's cell, phi from the LDS brick.
-template <int HK>
-__device__ __forceinline__ void cell_heaviside(const Brick &br, const HeatArgs &a, const double *ps, double *H)
+template <int HK, typename BR>
+__device__ __forceinline__ void cell_heaviside(const BR &br, const HeatArgs &a, const double *ps, double *H)
 {
     br.gather27(ps, H);
     interp3(H);
@@ -245,8 +244,8 @@ __device__ __forceinline__ void cell_heaviside(const Brick &br, const HeatArgs &
 // The velocity components are staged in LDS one at a time, in the region
 // vs, just before the pass that uses them (all threads of the brick call
 // this function: the staging barriers are uniform).
-template <bool TR, int HK, bool ISO = false>
-__device__ __forceinline__ void heat_conv_cell_apply(const Brick &br, const KMesh &m, const HeatArgs &a,
+template <bool TR, int HK, bool ISO, typename BR>
+__device__ __forceinline__ void heat_conv_cell_apply(const BR &br, const KMesh &m, const HeatArgs &a,
                                                      const double *ps, double *vs, double *u)
 {
     const double vol = m.hx * m.hy * m.hz;
@@ -260,7 +259,9 @@ __device__ __forceinline__ void heat_conv_cell_apply(const Brick &br, const KMes
         pin27(acc);
         pin27(u);
         __syncthreads(); // every thread is done with the previous component
-        br.stage_nodes<1, double>(m, a.u0 + d * nn, vs, nullptr, nullptr);
+        const double *src[1] = {a.u0 + d * nn};
+        double *const dst[1] = {vs};
+        br.template stage<1>(m, src, dst);
         __syncthreads();
         br.gather27(vs, v);
         interp3(v);
@@ -330,113 +331,122 @@ __device__ __forceinline__ void heat_conv_cell_apply(const Brick &br, const KMes
 }
 
 // CONV: 0 plain heat operator; 1 with the convective term; 2 its transpose
-// (FP64, level-set coefficients, no CG epilogue).  Bricks of 4 x 4 x BZ
-// cells, one thread per cell (BZ = 8: two wavefronts per brick).
-template <typename T, int MODE, int HK, bool CG, int CONV = 0, bool ISO = false, int BZ = BB>
-__global__ void __launch_bounds__(BrickDims<BZ>::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
-                                                                       T *__restrict__ y, T *__restrict__ face,
-                                                                       CGState *cg, RedWS red)
+// (FP64, level-set coefficients, no CG epilogue).  W sub-bricks per workgroup
+// (brick.hpp: Slab).  The cell work and the node sums of a sub-brick are the
+// wavefront's own; the nodes are staged, summed across the sub-bricks and
+// finished by the whole workgroup, row by row.  LDS: x (stays for the
+// Dirichlet rows and the CG epilogue); phi, then the node sums; and with
+// W > 1 a third region for the z exchange of the node sums (with W = 1 that
+// overlays phi), which holds the frozen temperature or one velocity
+// component before.
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W>
+__global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
+                                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
+                                                                 RedWS red)
 {
     static_assert(CONV == 0 || (std::is_same<T, double>::value && MODE == 0 && !CG), "convective form: FP64 only");
     static_assert(MODE != 2 || std::is_same<T, double>::value, "three-phase coefficients: FP64 only");
-    static_assert(CONV == 0 || BZ == BB, "convective form: 4x4x4 bricks (its velocity staging)");
-    using BR = BrickT<BZ>;
-    constexpr int NT = BR::NT;
-    // x stays resident (Dirichlet rows y = x and the CG epilogue read it);
-    // the second region takes phi (with one velocity component at a time, or
-    // the frozen temperature), then the z exchange of the node sums (for the
-    // transposed convective form, the cell results).
-    constexpr int NB = lds_field<T, BZ>(); // one staged field
-    constexpr int STAGE = CONV == 2 ? 27 * NT : ((CONV || MODE == 2) ? 2 * NB : NB);
-    static_assert(STAGE >= 9 * NT, "the second region takes the z exchange of the node sums");
-    constexpr int LDS_T = NB + STAGE;
-    __shared__ T lds[LDS_T];
-    __shared__ double red_lds[NT];
+    using SL = Slab<W>;
+    constexpr int NF = SL::template field<T>(), XCH = W > 1 ? 9 * SL::NT : 0;
+    static_assert(NF >= 9 * BNT, "with W = 1 the z exchange overlays phi");
+    constexpr int THIRD = (MODE == 2 || CONV != 0) && NF > XCH ? NF : XCH;
+    __shared__ T lds[2 * NF + THIRD + slab_xhi<W>()];
+    __shared__ double red_lds[W];
     if (CG) {
         if (cg->done) return; // converged or broken down: the rest of the batch is a no-op
     }
-    const BR br(m, threadIdx.x);
-    T *xs = lds;
-    T *ps = lds + NB;
-    if constexpr (MODE == 2) {
-        if (a.tc) {
-            const double *src[3] = {(const double *)x, (const double *)a.phi, (const double *)a.tc};
-            double *const dst[3] = {(double *)xs, (double *)ps, (double *)ps + NB};
-            br.template stage_nodes_wg<NT, 3>(m, threadIdx.x, src, dst, 0u);
-        } else {
-            br.template stage_nodes<2, T>(m, x, xs, (const T *)a.phi, ps);
-        }
-    } else if constexpr (sizeof(T) == 8) {
-        if (MODE != 1) br.template stage_nodes<2, T>(m, x, xs, (const T *)a.phi, ps);
-        else br.template stage_nodes<1, T>(m, x, xs, nullptr, nullptr);
+    const SL br(m, threadIdx.x);
+    T *xs = lds, *ps = lds + NF, *ts = lds + 2 * NF, *xhi = ts + THIRD;
+    const bool frozen = MODE == 2 && a.tc;
+    if (MODE == 2 && frozen) {
+        const T *src[3] = {x, (const T *)a.phi, (const T *)a.tc};
+        T *const dst[3] = {xs, ps, ts};
+        br.template stage<3>(m, src, dst);
+    } else if (MODE != 1) {
+        const T *src[2] = {x, (const T *)a.phi};
+        T *const dst[2] = {xs, ps};
+        br.template stage<2>(m, src, dst);
     } else {
-        if (MODE != 1) br.load_fields(m, x, xs, (const T *)a.phi, ps);
-        else br.load_fields(m, x, xs);
+        const T *src[1] = {x};
+        T *const dst[1] = {xs};
+        br.template stage<1>(m, src, dst);
     }
     __syncthreads();
 
-    const T vol = T(m.hx * m.hy * m.hz);
-    const T am_w = T(a.am) * vol;
-    const T ak_w = T(a.ak) * vol / T(kR * kR);
-    const T ihx = T(1.0 / (m.hx * m.hx)), ihy = T(1.0 / (m.hy * m.hy)), ihz = T(1.0 / (m.hz * m.hz));
     T u[27];
     if constexpr (CONV != 0) {
         br.gather27_dirichlet(m, xs, u);
-        heat_conv_cell_apply<CONV == 2, HK, ISO>(br, m, a, ps, ps + NB, u);
+        heat_conv_cell_apply<CONV == 2, HK, ISO>(br, m, a, ps, ts, u);
     } else {
+        const T vol = T(m.hx * m.hy * m.hz);
+        const T am_w = T(a.am) * vol;
+        const T ak_w = T(a.ak) * vol / T(kR * kR);
+        const T ihx = T(1.0 / (m.hx * m.hx)), ihy = T(1.0 / (m.hy * m.hy)), ihz = T(1.0 / (m.hz * m.hz));
         // With equal cell edges (ISO) 1/h^2 and the 1/4 of D'' = 2 D' go into
         // the stiffness weights, and the derivative passes take the integer
         // form (5 operations per line instead of 7).
         const T akw = ISO ? ak_w * ihx * T(0.25) : ak_w;
         T cm[27], ck[27];
         if constexpr (MODE == 2) {
-            heat_cell_coeffs3<HK>(br, m, a, (const double *)ps, (const double *)ps + NB, cm, ck,
+            heat_cell_coeffs3<HK>(br, m, a, (const double *)ps, (const double *)ts, cm, ck,
                                   ISO ? double(ihx) * 0.25 : 1.0);
-        } else if (MODE == 0) {
+        } else if constexpr (MODE == 0) {
             T ph[27];
             br.gather27(ps, ph);
             interp3(ph);
             heat_cell_coeffs<T, 0, HK>(a, ph, nullptr, nullptr, am_w, akw, cm, ck);
         } else {
             const int64_t cell = br.valid ? br.cell_index(m) : 0;
-            heat_cell_coeffs<T, 1, 0>(a, nullptr, (const T *)a.kq + 27 * cell, (const T *)a.rcq + 27 * cell, am_w,
-                                      akw, cm, ck);
+            heat_cell_coeffs<T, 1, 0>(a, nullptr, (const T *)a.kq + 27 * cell, (const T *)a.rcq + 27 * cell, am_w, akw,
+                                      cm, ck);
         }
         br.gather27_dirichlet(m, xs, u);
         if constexpr (ISO) heat_cell_apply_iso<T>(u, cm, ck);
         else heat_cell_apply<T>(u, cm, ck, ihx, ihy, ihz);
     }
-    __syncthreads(); // the phi region is now reused for the node sums
-    if constexpr (CONV == 2) {
-        // through LDS: the transposed convective form has no registers to
-        // spare for the register exchange
-        T *E = ps;
-        br.store_cell(E, u);
-        __syncthreads();
-        br.template for_owned_nodes<T>(m, [&](int ai, int bi, int ci, int, int64_t, bool, int) {
-            u[ai + 3 * bi + 9 * ci] = br.node_sum(E, ai, bi, ci);
-        });
-    } else {
-        br.assemble27(u, ps);
-    }
+    __syncthreads(); // phi and the third region no longer read
+    br.assemble(u, W > 1 ? ts + 9 * BNT * br.w : ps, ps, xhi);
+    __syncthreads();
 
-    // Owned nodes: complete nodes go to y, shared ones to the face buffer;
-    // Dirichlet rows get y_i = x_i (shared ones in the combine pass).
-    // x.Ax = sum over bricks of x_i times the brick's partial sum at node i,
-    // with x_i^2 for a Dirichlet node counted once, by the brick that
-    // finishes it.
     double energy = 0.0;
-    T *fb = face + (int64_t)br.brick * BR::NFACE;
-    br.template for_owned_nodes<T>(m, [&](int ai, int bi, int ci, int l, int64_t g, bool constrained, int sh) {
-        const T xv = xs[l], s = u[ai + 3 * bi + 9 * ci];
-        if (CG) energy += constrained ? ((sh & 2) ? 0.0 : (double)xv * (double)xv) : (double)xv * (double)s;
-        T *dst = sh ? fb + br.fslot(ai, bi, ci) : y + g;
-        *dst = constrained ? xv : s;
-    });
+    T v[SL::NV], xv[SL::NV];
+    br.node_values(m, ps, xhi, v);
+    if (CG || br.dirichlet_faces(m)) {
+        br.read_nodes(m, xs, xv);
+    } else {
+#pragma unroll
+        for (int k = 0; k < SL::NV; ++k) xv[k] = T(0);
+    }
+    finish_nodes<T, CG>(m, br, y, face, v, xv, energy);
     if (CG) {
-        // one partial per brick; the alpha kernel sums them in brick order
-        const double tot = block_sum<NT>(energy, red_lds);
+        // one partial per slab; the alpha kernel sums them in slab order
+        double tot = wave_total(energy);
+        if constexpr (W > 1) {
+            if (br.t == 0) red_lds[br.w] = tot;
+            __syncthreads();
+            tot = red_lds[0];
+#pragma unroll
+            for (int k = 1; k < W; ++k) tot += red_lds[k];
+        }
         write_partials<1>(&tot, red.partials, gridDim.x, (unsigned)br.brick);
+    }
+}
+
+// alpha = rz / p.Ap from the partials of a CG-mode apply, by one workgroup.
+template <int NT>
+__device__ __forceinline__ void cg_set_alpha(CGState *cg, const double *__restrict__ partials, unsigned n)
+{
+    __shared__ double red[NT];
+    const double pAp = sum_partials<NT>(partials, n, 0, red);
+    if (threadIdx.x == 0) {
+        cg->pAp = pAp;
+        if (!(pAp > 0.0) || !isfinite(pAp)) {
+            cg->breakdown = 1;
+            cg->done = 1;
+            cg->alpha = 0.0;
+        } else {
+            cg->alpha = cg->rz / pAp;
+        }
     }
 }
 
@@ -448,72 +458,67 @@ __global__ void __launch_bounds__(BrickDims<BZ>::NT) heat_apply_kernel(KMesh m, 
 // iteration.  A breakdown sets done here; a workgroup of this launch that
 // then skips its nodes leaves q incomplete, which no later step of the
 // solve reads.
-template <typename T, bool CG, int DMODE = 1, int BZ = BB>
+template <typename T, int DMODE>
 __global__ void __launch_bounds__(BNT * CBW) face_combine_brick_kernel(KMesh m, const T *__restrict__ face,
-                                                                 const T *__restrict__ x, T *__restrict__ y,
-                                                                 CGState *cg, const double *__restrict__ partials,
-                                                                 unsigned nbricks)
+                                                                       T *__restrict__ y)
+{
+    combine_brick<T, DMODE>(m, face, nullptr, y);
+}
+
+// The same for an apply: slabs, y = x on Dirichlet nodes, and alpha with CG.
+template <typename T, bool CG, int W>
+__global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__restrict__ face, const T *__restrict__ x,
+                                                           T *__restrict__ y, CGState *cg,
+                                                           const double *__restrict__ partials, unsigned nslabs)
 {
     if (CG) {
         if (cg->done) return;
+        if (blockIdx.x == 0) cg_set_alpha<SCT>(cg, partials, nslabs);
     }
-    if (CG && blockIdx.x == 0) {
-        // before the combine, which lets wavefronts without a brick leave
-        __shared__ double red[BNT * CBW];
-        const double pAp = sum_partials<BNT * CBW>(partials, nbricks, 0, red);
-        if (threadIdx.x == 0) {
-            cg->pAp = pAp;
-            if (!(pAp > 0.0) || !isfinite(pAp)) {
-                cg->breakdown = 1;
-                cg->done = 1;
-                cg->alpha = 0.0;
-            } else {
-                cg->alpha = cg->rz / pAp;
-            }
-        }
-    }
-    combine_brick<T, DMODE, BZ>(m, face, x, y);
+    combine_slabs<T, W>(m, face, x, y);
 }
-
-// Brick depth of the FP32 applies (the multigrid levels): 4x4x8 cells, two
-// wavefronts per brick.  Against 4x4x4 bricks this halves the internal z
-// planes of the brick grid, and with them the face-buffer partials and the
-// combine pass's z-shared nodes (128^3 FP32 whole apply about 5 % faster).
-// The FP64 applies keep 4x4x4 bricks: there the deeper brick made the brick
-// kernel slower by as much as it made the combine faster.
-constexpr int HEAT_BZ32 = 8;
 
 int64_t face_buffer_elems(const KMesh &m)
 {
-    const int64_t b4 = n_bricks<BB>(m) * BrickDims<BB>::NFACE;
-    const int64_t b8 = n_bricks<HEAT_BZ32>(m) * BrickDims<HEAT_BZ32>::NFACE;
+    // the larger of the bricks' slots (those of any slab layout are fewer)
+    // and 1683 per 4x4x8 cells, which is what mf_operator_apply_noalloc's
+    // fixed scratch admits
+    const int64_t b4 = n_bricks(m) * BFACE;
+    const int64_t b8 = (int64_t)ceil_div(m.nx, BB) * ceil_div(m.ny, BB) * ceil_div(m.nz, 8) * 1683;
     return b4 > b8 ? b4 : b8;
 }
 
-// One apply: the brick kernel, then the combine pass of its shared nodes
-// (with CG, alpha from the bricks' partials of p.Ap).  With timing on, the
-// events are attached to the brick kernel's own dispatch (they record its
+// One apply: the slab kernel, then the combine pass of its shared nodes
+// (with CG, alpha from the slabs' partials of p.Ap).  With timing on, the
+// events are attached to the slab kernel's own dispatch (they record its
 // start and end, not the neighbouring queue packets).
+template <typename T, int MODE, int HK, bool CGF, int CV, bool ISO, int W>
+static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face, CGState *cg,
+                                   const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
+{
+    const unsigned ns = (unsigned)n_slabs<W>(m);
+    constexpr int NT = Slab<W>::NT;
+    if (ev0)
+        hipExtLaunchKernelGGL(heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, W>, dim3(ns), dim3(NT), 0, s, ev0, ev1, 0, m,
+                              a, (const T *)x, (T *)y, (T *)face, cg, r);
+    else
+        heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, W><<<ns, NT, 0, s>>>(m, a, (const T *)x, (T *)y, (T *)face, cg, r);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // a single slab shares nothing; alpha from its partial
+    if (ns == 1) return CGF ? cg_alpha(cg, &r, ns, s) : hipSuccess;
+    constexpr unsigned PER = SCT / combine_lanes<W>();
+    slab_combine_kernel<T, CGF, W><<<(ns + PER - 1) / PER, SCT, 0, s>>>(
+        m, (const T *)face, (const T *)x, (T *)y, CGF ? cg : nullptr, CGF ? r.partials : nullptr, CGF ? ns : 0u);
+    return hipGetLastError();
+}
+
 template <typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
 static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face,
                                     CGState *cg, const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    constexpr int BZ = sizeof(T) == 4 ? HEAT_BZ32 : BB;
-    constexpr int NT = BrickDims<BZ>::NT;
-    const unsigned nb = (unsigned)n_bricks<BZ>(m);
-    if (ev0)
-        hipExtLaunchKernelGGL(heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, BZ>, dim3(nb), dim3(NT), 0, s, ev0, ev1, 0,
-                              m, a, (const T *)x, (T *)y, (T *)face, cg, r);
-    else
-        heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, BZ><<<nb, NT, 0, s>>>(m, a, (const T *)x, (T *)y, (T *)face, cg, r);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // a single brick shares nothing; alpha from its partial
-    if (nb == 1) return CGF ? cg_alpha(cg, &r, nb, s) : hipSuccess;
-    constexpr int BPW = BNT * CBW / CombineLanes<BZ>::value; // bricks per combine workgroup
-    face_combine_brick_kernel<T, CGF, 1, BZ><<<(nb + BPW - 1) / BPW, BNT * CBW, 0, s>>>(
-        m, (const T *)face, (const T *)x, (T *)y, CGF ? cg : nullptr, CGF ? r.partials : nullptr, CGF ? nb : 0u);
-    return hipGetLastError();
+    if (use_wide_slabs(m, CV != 0 || MODE != 0 || HK != 0)) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
+    return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 1>(m, a, x, y, face, cg, r, s, ev0, ev1);
 }
 
 hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x, void *y, void *face, CGState *cg,
@@ -735,8 +740,8 @@ static hipError_t heat_diagonal_launch(const KMesh &m, const HeatArgs &a, int fp
     // DMODE 2: Dirichlet rows 1; 4: the same, and the reciprocals of the others
     constexpr int DM = INV ? 4 : 2;
     const unsigned wg = (nb + CBW - 1) / CBW;
-    if (fp32) face_combine_brick_kernel<float, false, DM><<<wg, BNT * CBW, 0, s>>>(m, ff, nullptr, df, nullptr, nullptr, 0);
-    else face_combine_brick_kernel<double, false, DM><<<wg, BNT * CBW, 0, s>>>(m, fd, nullptr, dd, nullptr, nullptr, 0);
+    if (fp32) face_combine_brick_kernel<float, DM><<<wg, BNT * CBW, 0, s>>>(m, ff, df);
+    else face_combine_brick_kernel<double, DM><<<wg, BNT * CBW, 0, s>>>(m, fd, dd);
     return hipGetLastError();
 }
 
@@ -755,14 +760,6 @@ hipError_t heat_diagonal(const KMesh &m, const HeatArgs &a, int fp32, void *diag
 // Serves the coarsest multigrid level, whose right-hand side and solution
 // are FP32.  Stops when ||r|| <= rtol ||b||, at maxit, or on breakdown.
 // ---------------------------------------------------------------------------
-// Sum over the wavefront, identical in every lane.
-__device__ __forceinline__ double wave_total(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return __shfl(v, 0, 64);
-}
-
 // INV: workgroup c solves A x = e_c and writes x as column c of inv (FP64,
 // column-major, n_nodes rows): the columns of A^-1, all solved at once.
 template <int HK, bool INV = false>
@@ -1034,8 +1031,7 @@ hipError_t heat_grad(const KMesh &m, const HeatArgs &a, const double *T, const d
     if (e != hipSuccess || !dphi || a.mode != 0) return e;
     // the level-set gradient sums over Dirichlet nodes too (DMODE 0)
     if (nb == 1) return hipSuccess;
-    face_combine_brick_kernel<double, false, 0><<<(nb + CBW - 1) / CBW, BNT * CBW, 0, s>>>(
-        m, (const double *)face, nullptr, dphi, nullptr, nullptr, 0);
+    face_combine_brick_kernel<double, 0><<<(nb + CBW - 1) / CBW, BNT * CBW, 0, s>>>(m, (const double *)face, dphi);
     return hipGetLastError();
 }
 
