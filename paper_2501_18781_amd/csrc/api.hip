@@ -9,7 +9,9 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "ctx.hpp"
@@ -120,7 +122,8 @@ mf_status mf_create(const mf_mesh *mesh, mf_ctx **out)
     }
     // reduction workspace: enough for one partial per heat brick and 64 sets of 1024 blocks
     const int64_t nbricks = ((k.nx + 3) / 4) * (int64_t)((k.ny + 3) / 4) * ((k.nz + 3) / 4);
-    int64_t cap = nbricks > 64 * 1024 ? nbricks : 64 * 1024;
+    // (the CG keeps the partials of its update and of its apply side by side)
+    int64_t cap = std::max<int64_t>(nbricks + 2 * CG_MAX_UPDATE, 64 * 1024);
     c->cap = (unsigned)cap;
     bool ok = hipMalloc((void **)&c->partials, sizeof(double) * cap) == hipSuccess &&
               hipMalloc((void **)&c->cg, sizeof(CGState)) == hipSuccess &&
@@ -548,7 +551,9 @@ mf_status cg_solve(mf_ctx *c, const mf_operator *op, int precond, const double *
         HIPCHK(c, heat_diagonal(c->km, ha, 0, dinv, c->face, s, true));
     }
     RedWS red = redws(c);
-    HIPCHK(c, cg_init(c->cg, b, dinv, x, r, p, n, rtol, maxit, 0, &red, s));
+    const unsigned ns = heat_cg_slabs(c->km, ha); // 0: four launches per iteration, else two (see vec.hip)
+    const bool two = ns != 0;
+    HIPCHK(c, cg_init(c->cg, b, dinv, x, r, p, n, rtol, maxit, two ? CG_TWO_LAUNCH : CG_PLAIN, &red, s));
     // Iterations are launched in batches, each followed by a copy of the
     // state that the host polls.  While the host waits for that copy and
     // decides, the GPU already runs one more iteration (launched before the
@@ -558,11 +563,22 @@ mf_status cg_solve(mf_ctx *c, const mf_operator *op, int precond, const double *
     // extrapolation to the threshold): that only sets how often the host
     // polls, never what is computed.
     HIPCHK(c, poll_events(c));
+    const unsigned nu = cg_update_blocks(ns);
+    double *const rpart = red.partials, *const ppart = rpart + 2 * CG_MAX_UPDATE;
+    double *pcur = p, *pnext = p + n; // a workspace vector holds three nodal ones
     auto iterate = [&](int k) -> hipError_t {
         for (int i = 0; i < k; ++i) {
-            hipError_t e = heat_apply(c->km, ha, 0, p, q, c->face, c->cg, &red, s);
-            if (e == hipSuccess) e = cg_resid(c->cg, dinv, r, q, n, &red, s);
-            if (e == hipSuccess) e = cg_step(c->cg, x, r, p, n, &red, s);
+            hipError_t e;
+            if (two) {
+                const CGDir dir{r, pcur, pnext, x, rpart, nu};
+                e = heat_cg_apply(c->km, ha, dir, q, c->face, c->cg, ppart, s);
+                if (e == hipSuccess) e = cg_update(c->km, c->cg, ns, ppart, c->face, q, pnext, dinv, r, rpart, s);
+                std::swap(pcur, pnext);
+            } else {
+                e = heat_apply(c->km, ha, 0, p, q, c->face, c->cg, &red, s);
+                if (e == hipSuccess) e = cg_resid(c->cg, dinv, r, q, n, &red, s);
+                if (e == hipSuccess) e = cg_step(c->cg, x, r, p, n, &red, s);
+            }
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
@@ -572,6 +588,7 @@ mf_status cg_solve(mf_ctx *c, const mf_operator *op, int precond, const double *
     int iters_prev = 0;
     HIPCHK(c, iterate(batch));
     for (;;) {
+        if (two) HIPCHK(c, cg_check(c->cg, rpart, nu, s));
         HIPCHK(c, hipMemcpyAsync(c->h_state, c->cg, sizeof(CGState), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipEventRecord(c->poll_ev[0], s));
         HIPCHK(c, iterate(1)); // runs while the host polls
@@ -594,9 +611,10 @@ mf_status cg_solve(mf_ctx *c, const mf_operator *op, int precond, const double *
         launched += batch;
     }
     // The state copied at the last poll is final when it says done: the
-    // iteration queued behind it only sets `run`.  Otherwise (the iteration
+    // iteration queued behind it only sets `run`, or completes x.  Otherwise (the iteration
     // limit guard) read the state again.
     if (!c->h_state->done) {
+        if (two) HIPCHK(c, cg_check(c->cg, rpart, nu, s));
         HIPCHK(c, hipMemcpyAsync(c->h_state, c->cg, sizeof(CGState), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
     }

@@ -825,6 +825,68 @@ template <int W_, int R_ = (W_ == 1 ? 10 : 8 * W_ + 4)> struct Slab {
             for (int f = 0; f < NF; ++f) dst[f][at[k]] = v[k][f];
     }
 
+    // Stage as above with the first field formed on the way, p = z + beta p_old
+    // from src[0] = z and src[1] = p_old (dst[0] takes p, dst[f] src[f + 1]):
+    // the direction update of a CG iteration, with the previous iteration's
+    // x += alpha p_old.  p also goes to pn.  x and pn: each node from the one
+    // slab that owns it.  mid(alpha, beta) runs once all reads are issued; where
+    // it returns false (in every thread alike), only x is updated and false
+    // is returned.
+    template <int NF, typename T, typename M>
+    __device__ __forceinline__ bool stage_direction(const KMesh &m, const T *const (&src)[NF], T *const (&dst)[NF - 1],
+                                                    T *__restrict__ pn, T *__restrict__ x, M mid) const
+    {
+        __amdgpu_buffer_rsrc_t rs[NF + 1];
+        const int64_t o = node_index(m, 2 * c0x, 2 * c0y, 2 * c0z);
+        const int64_t rem = ((int64_t)m.NX * m.NY * m.NZ - o) * (int64_t)sizeof(T);
+        const int nrec = (int)(unsigned)(rem > 0xFFFFFFFFll ? 0xFFFFFFFFll : rem);
+#pragma unroll
+        for (int f = 0; f <= NF; ++f)
+            rs[f] = __builtin_amdgcn_make_buffer_rsrc((void *)((f < NF ? src[f] : x) + o), 0, nrec, 0x00020000);
+        const int ox = owned_end(m.nx, c0x, CX), oy = owned_end(m.ny, c0y, BB), oz = owned_end(m.nz, c0z, BB);
+        const int lx = tid % RX;
+        T v[NV][NF + 1];
+        auto read = [&](int k, unsigned off, bool okx, int ly, int lz, bool ok) MF_INLINE {
+            const unsigned vofs = ok ? (unsigned)sizeof(T) * off : 0u;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[k][f] = Brick::nodal_load<T>(rs[f], vofs, 0);
+            v[k][NF] = Brick::nodal_load<T>(rs[NF], okx && ly <= oy && lz <= oz ? vofs : 0u, 0);
+        };
+        for_rows<T>(m, [&](auto k, int, unsigned off, int ly, int lz, bool ok) MF_INLINE {
+            read(k, off, lx <= ox, ly, lz, ok);
+        });
+        for_edge<T>(m, [&](auto k, int, unsigned off, int ly, int lz, bool ok) MF_INLINE {
+            read(STEPS + k, off, RX <= ox, ly, lz, ok);
+        });
+        T alpha, beta;
+        const bool go = mid(alpha, beta);
+        T *const pb = pn + o, *const xb = x + o;
+        auto put = [&](int k, int slot, unsigned off, bool okx, int ly, int lz, bool ok) MF_INLINE {
+            const bool own = ok && okx && ly <= oy && lz <= oz;
+            if (own) xb[off] = v[k][NF] + alpha * v[k][1];
+            if (!go) return;
+            const T p = v[k][0] + beta * v[k][1];
+            const int at = ok ? slot : SP; // as in stage
+            dst[0][at] = p;
+#pragma unroll
+            for (int f = 2; f < NF; ++f) dst[f - 1][at] = v[k][f];
+            if (own) pb[off] = p;
+        };
+        for_rows<T>(m, [&](auto k, int slot, unsigned off, int ly, int lz, bool ok) MF_INLINE {
+            put(k, slot, off, lx <= ox, ly, lz, ok);
+        });
+        for_edge<T>(m, [&](auto k, int slot, unsigned off, int ly, int lz, bool ok) MF_INLINE {
+            put(STEPS + k, slot, off, RX <= ox, ly, lz, ok);
+        });
+        return go;
+    }
+    // Last local node index that this slab, not the next one, owns along a
+    // direction of n cells, with `size` cells per slab from cell c0 on.
+    static __device__ __forceinline__ int owned_end(int n, int c0, int size)
+    {
+        return c0 + size < n ? 2 * size - 1 : 2 * (n - c0);
+    }
+
     // The node sums at the visited nodes (from v[STEPS] on: the edge), all read
     // together: the node array, plus the left sub-brick's part on the planes
     // between sub-bricks (whose threads are the same in every step).

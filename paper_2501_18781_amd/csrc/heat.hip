@@ -339,11 +339,15 @@ __device__ __forceinline__ void heat_conv_cell_apply(const BR &br, const KMesh &
 // W > 1 a third region for the z exchange of the node sums (with W = 1 that
 // overlays phi), which holds the frozen temperature or one velocity
 // component before.
-template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W>
-__global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
-                                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
-                                                                 RedWS red)
+// CG: the epilogue sums p.Ap.  DIR (with CG): x is p = z + beta p_old, formed in
+// the staging from the previous iteration's residual partials (CGDir); once
+// converged only x is completed.
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W, bool DIR>
+__device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &a, const T *__restrict__ x,
+                                                T *__restrict__ y, T *__restrict__ face, CGState *cg,
+                                                double *partials, const CGDir &dir)
 {
+    static_assert(!DIR || (CG && W == 1 && std::is_same<T, double>::value), "the direction update is CG's");
     static_assert(CONV == 0 || (std::is_same<T, double>::value && MODE == 0 && !CG), "convective form: FP64 only");
     static_assert(MODE != 2 || std::is_same<T, double>::value, "three-phase coefficients: FP64 only");
     using SL = Slab<W>;
@@ -352,13 +356,50 @@ __global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatAr
     constexpr int THIRD = (MODE == 2 || CONV != 0) && NF > XCH ? NF : XCH;
     __shared__ T lds[2 * NF + THIRD + slab_xhi<W>()];
     __shared__ double red_lds[W];
-    if (CG) {
+    if (DIR) {
+        if (cg->ended || cg->breakdown == 1) return; // both written by the update kernel only
+    } else if (CG) {
         if (cg->done) return; // converged or broken down: the rest of the batch is a no-op
     }
     const SL br(m, threadIdx.x);
     T *xs = lds, *ps = lds + NF, *ts = lds + 2 * NF, *xhi = ts + THIRD;
     const bool frozen = MODE == 2 && a.tc;
-    if (MODE == 2 && frozen) {
+    if constexpr (DIR) {
+        // Every workgroup sums the residual partials in the same order.  The
+        // fields of cg read in this launch are written by other launches only.
+        auto mid = [&](double &alpha, double &beta) MF_INLINE -> bool {
+            alpha = cg->alpha;
+            beta = 0.0;
+            const int it = cg->iter;
+            if (it == 0) return true; // no residual yet: p = z (and p_old = 0, alpha = 0)
+            const double rz = wave_total(lane_partials(dir.partials, dir.nb, br.t));
+            const double rr = wave_total(lane_partials(dir.partials + dir.nb, dir.nb, br.t));
+            const bool bad = !isfinite(rz) || !isfinite(rr);
+            const bool stop = bad || rr <= cg->thresh2 || it >= cg->maxit;
+            beta = rz / cg->rz_old;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                cg->rr = rr;
+                cg->rz = rz;
+                cg->beta = beta;
+                if (bad) cg->breakdown = 2;
+                if (stop) cg->done = 1;
+            }
+            return !stop;
+        };
+        if (frozen) {
+            const T *src[4] = {dir.z, dir.p_old, (const T *)a.phi, (const T *)a.tc};
+            T *const dst[3] = {xs, ps, ts};
+            if (!br.template stage_direction<4>(m, src, dst, dir.pn, dir.x, mid)) return;
+        } else if (MODE != 1) {
+            const T *src[3] = {dir.z, dir.p_old, (const T *)a.phi};
+            T *const dst[2] = {xs, ps};
+            if (!br.template stage_direction<3>(m, src, dst, dir.pn, dir.x, mid)) return;
+        } else {
+            const T *src[2] = {dir.z, dir.p_old};
+            T *const dst[1] = {xs};
+            if (!br.template stage_direction<2>(m, src, dst, dir.pn, dir.x, mid)) return;
+        }
+    } else if (MODE == 2 && frozen) {
         const T *src[3] = {x, (const T *)a.phi, (const T *)a.tc};
         T *const dst[3] = {xs, ps, ts};
         br.template stage<3>(m, src, dst);
@@ -428,8 +469,23 @@ __global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatAr
 #pragma unroll
             for (int k = 1; k < W; ++k) tot += red_lds[k];
         }
-        write_partials<1>(&tot, red.partials, gridDim.x, (unsigned)br.brick);
+        write_partials<1>(&tot, partials, gridDim.x, (unsigned)br.brick);
     }
+}
+
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W>
+__global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
+                                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
+                                                                 RedWS red)
+{
+    heat_apply_slab<T, MODE, HK, CG, CONV, ISO, W, false>(m, a, x, y, face, cg, red.partials, CGDir{});
+}
+
+template <int MODE, int HK, bool ISO>
+__global__ void __launch_bounds__(BNT) heat_cg_apply_kernel(KMesh m, HeatArgs a, CGDir dir, double *__restrict__ q,
+                                                            double *__restrict__ face, CGState *cg, double *ppart)
+{
+    heat_apply_slab<double, MODE, HK, true, 0, ISO, 1, true>(m, a, nullptr, q, face, cg, ppart, dir);
 }
 
 // alpha = rz / p.Ap from the partials of a CG-mode apply, by one workgroup.
@@ -513,11 +569,16 @@ static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void
     return hipGetLastError();
 }
 
+static bool wide_slabs(const KMesh &m, const HeatArgs &a)
+{
+    return use_wide_slabs(m, a.conv != 0 || a.mode != 0 || a.hkind != 0);
+}
+
 template <typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
 static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face,
                                     CGState *cg, const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    if (use_wide_slabs(m, CV != 0 || MODE != 0 || HK != 0)) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
+    if (wide_slabs(m, a)) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
     return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 1>(m, a, x, y, face, cg, r, s, ev0, ev1);
 }
 
@@ -579,6 +640,42 @@ hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x
     default:
         return hipErrorInvalidValue;
     }
+}
+
+// Slabs of one brick, and few enough of them (an x extent that leaves slabs of
+// four half empty is no bound) for every update workgroup to sum their partials.
+unsigned heat_cg_slabs(const KMesh &m, const HeatArgs &a)
+{
+    const int64_t nb = n_bricks(m);
+    return wide_slabs(m, a) || nb >= 3600 ? 0u : (unsigned)nb;
+}
+
+hipError_t heat_cg_apply(const KMesh &m, const HeatArgs &a, const CGDir &dir, double *q, void *face, CGState *cg,
+                         double *ppart, hipStream_t s)
+{
+    const unsigned ns = heat_cg_slabs(m, a);
+    if (!face || a.conv || ns == 0) return hipErrorInvalidValue;
+    const int hk = a.mode == 1 ? 0 : (a.hkind ? 1 : 0);
+    const bool iso = m.hx == m.hy && m.hy == m.hz;
+    const int key = (iso ? 8 : 0) | (a.mode << 1) | hk;
+    double *fb = (double *)face;
+    switch (key) {
+#define CG_CASE(K, MODE, HK, ISO) \
+    case K: heat_cg_apply_kernel<MODE, HK, ISO><<<ns, BNT, 0, s>>>(m, a, dir, q, fb, cg, ppart); break;
+        CG_CASE(0, 0, 0, false)
+        CG_CASE(1, 0, 1, false)
+        CG_CASE(2, 1, 0, false)
+        CG_CASE(4, 2, 0, false)
+        CG_CASE(5, 2, 1, false)
+        CG_CASE(8, 0, 0, true)
+        CG_CASE(9, 0, 1, true)
+        CG_CASE(10, 1, 0, true)
+        CG_CASE(12, 2, 0, true)
+        CG_CASE(13, 2, 1, true)
+#undef CG_CASE
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -67,6 +67,7 @@ struct CGState {
     double rzprev; // flexible CG: r_{k+1} . z_k
     int iter, maxit, done, breakdown, flexible;
     int run;   // set by the CG residual kernel: whether it ran this iteration
+    int ended; // CG in two launches: done was seen by an update kernel (the apply before it completed x)
     int xpend; // flexible CG: x still lacks the last alpha p
 };
 
@@ -90,6 +91,22 @@ struct KTiming {
 hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x, void *y, void *face, CGState *cg,
                       const RedWS *red, hipStream_t s, const KTiming *t = nullptr);
 int64_t face_buffer_elems(const KMesh &m);
+// The apply of one CG iteration with the direction update in its staging: the
+// residual totals from dir's partials, beta and the convergence test; the
+// previous iteration's x += alpha p_old; then, unless converged, p = z + beta
+// p_old to pn; q = A p on the nodes that no two slabs share and the slabs'
+// partial sums of the others to `face`; partials of p.Ap to ppart, one per
+// slab.  For the meshes for which heat_cg_slabs is not 0.
+struct CGDir {
+    const double *z, *p_old;
+    double *pn, *x;
+    const double *partials; // of r.z and r.r, nb each
+    unsigned nb;
+};
+hipError_t heat_cg_apply(const KMesh &m, const HeatArgs &a, const CGDir &dir, double *q, void *face, CGState *cg,
+                         double *ppart, hipStream_t s);
+// The slabs of heat_cg_apply, or 0 where a CG iteration in four launches is better.
+unsigned heat_cg_slabs(const KMesh &m, const HeatArgs &a);
 hipError_t heat_qp_coeffs(const KMesh &m, const HeatArgs &a, double *kq, double *rcq, hipStream_t s);
 // Whole FP64 Jacobi-CG solve (x0 = 0) in one single-workgroup launch, for a
 // LEVELSET-mode operator on a mesh of at most 4 cells per direction; b and x
@@ -168,10 +185,12 @@ hipError_t dgs_step(const double *V, int64_t ld, int j, bool full, double *u, do
 hipError_t block3_invert(double *blocks, int64_t nn, hipStream_t s);
 hipError_t block3_apply(const double *binv, const double *x, double *y, int64_t nn, hipStream_t s);
 
-// x = 0, p = D^-1 b and r = D^-1 b (the z of cg_resid; flexible: r = b, p = 0), rz and |b|^2 into st.
+// x = 0, p = D^-1 b and r = D^-1 b (the z of cg_resid), or p = 0 (two
+// launches), or r = b and p = 0 (flexible); rz and |b|^2 into st.
+enum CGForm { CG_PLAIN, CG_FLEXIBLE, CG_TWO_LAUNCH };
 hipError_t cg_init(CGState *st, const double *b, const double *dinv, double *x, double *r, double *p, int64_t n,
-                   double rtol, int maxit, int flexible, const RedWS *red, hipStream_t s);
-// alpha = rz / p.Ap from the nb per-brick partials of a CG-mode apply.
+                   double rtol, int maxit, int form, const RedWS *red, hipStream_t s);
+// alpha = rz / p.Ap from the nb per-slab partials of a CG-mode apply.
 hipError_t cg_alpha(CGState *st, const RedWS *red, unsigned nb, hipStream_t s);
 // With the diagonal preconditioner (dinv non-null) the vector r holds
 // z = D^-1 r: z -= alpha D^-1 q and the partials of r.z and r.r with
@@ -180,6 +199,15 @@ hipError_t cg_resid(CGState *st, const double *dinv, double *r, const double *q,
                     hipStream_t s);
 // beta and the convergence test from cg_resid's partials; x += alpha p, p = z + beta p
 hipError_t cg_step(CGState *st, double *x, const double *z, double *p, int64_t n, const RedWS *red, hipStream_t s);
+// What follows heat_cg_apply: alpha from its nslabs partials, z -= alpha D^-1 q
+// with the shared nodes of q summed from `face`; partials of r.z and r.r,
+// cg_update_blocks of each (at most CG_MAX_UPDATE), to rpart.
+constexpr unsigned CG_MAX_UPDATE = 512;
+unsigned cg_update_blocks(unsigned nslabs);
+hipError_t cg_update(const KMesh &m, CGState *st, unsigned nslabs, const double *ppart, const void *face,
+                     const double *q, const double *p, const double *dinv, double *z, double *rpart, hipStream_t s);
+// The residual totals and the convergence test into st, for a host poll.
+hipError_t cg_check(CGState *st, const double *rpart, unsigned nb, hipStream_t s);
 // Flexible-CG pieces (FP32 preconditioner output z, supplied by the caller):
 // r -= alpha q, r32 = fl32(r), r.r and r.z_old, convergence test;
 hipError_t fcg_resid(CGState *st, double *r, const double *q, const float *zold, float *r32, int64_t n,

@@ -530,6 +530,18 @@ __device__ __forceinline__ void write_partials(const double *v, double *partials
     }
 }
 
+// One lane's share of a set of n partials, entries lane, lane + 64, ..., eight
+// loads in flight.
+__device__ __forceinline__ double lane_partials(const double *p, unsigned n, unsigned lane)
+{
+    double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (unsigned b = lane; b < n; b += 512) {
+#pragma unroll
+        for (unsigned k = 0; k < 8; ++k) s[k] += b + 64 * k < n ? p[b + 64 * k] : 0.0;
+    }
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+
 // Total of partial set i (nblocks entries written by an earlier launch),
 // returned to every thread of an NT-thread block.  Thread t sums entries
 // t, t + NT, ... with four interleaved accumulators (combined in a fixed

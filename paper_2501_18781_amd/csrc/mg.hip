@@ -793,7 +793,7 @@ extern "C" mf_status mf_mg_cg_solve(mf_mg *mg, const double *b, double *x, doubl
     // direction, apply and residual kernels are no-ops and the V-cycle's
     // output is unused.  The state read at the last poll is final: the
     // finishing kernel only adds the pending alpha p to x.
-    HIPCHK(c, cg_init(c->cg, b, nullptr, x, r, p, n, rtol, maxit, 1, &red, s));
+    HIPCHK(c, cg_init(c->cg, b, nullptr, x, r, p, n, rtol, maxit, CG_FLEXIBLE, &red, s));
     HIPCHK(c, vcvt_d2f(b, top.b, n, s)); // r = b
     if ((st = vcycle(mg, ltop, s))) return st;
     HIPCHK(c, fcg_direction(c->cg, r, top.x, p, x, n, &red, s));

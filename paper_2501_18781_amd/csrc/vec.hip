@@ -13,6 +13,7 @@
 #include <atomic>
 #include <cstdint>
 
+#include "brick.hpp"
 #include "kernels.hpp"
 
 namespace mf {
@@ -735,9 +736,9 @@ hipError_t block3_apply(const double *B, const double *x, double *y, int64_t nn,
 // CG (preconditioned with a diagonal, Saad Alg. 9.1).  With the diagonal
 // preconditioner the solver keeps z = D^-1 r in place of r (r = z / D^-1
 // where a dot product needs it), so that the direction update needs no
-// D^-1.  One iteration is
-//   apply   q = A p, per-brick partials of p.q     (heat.hip, CG mode)
-//   alpha   alpha = rz / p.q                        (one workgroup)
+// D^-1.  One iteration in four launches is
+//   apply   q = A p, per-slab partials of p.q      (heat.hip, CG mode)
+//   combine the shared nodes of q; alpha = rz / p.q (its first workgroup)
 //   resid   z -= alpha D^-1 q; partials of r.z and r.r; iteration count,
 //           rz_old = rz                              (reads z, q, D^-1; writes z)
 //   step    every workgroup sums the residual partials in the same order:
@@ -747,16 +748,40 @@ hipError_t block3_apply(const double *B, const double *x, double *y, int64_t nn,
 // Nine vector passes per iteration (without a preconditioner z = r).
 // Each thread keeps CG_UNROLL elements of its grid-stride sequence in flight.
 //
-// The done flag: a kernel that reads it at entry must not write it (another
-// workgroup of the same launch could start after the write).  The step
-// kernel writes it, so it tests `run` instead, which the residual kernel
-// (an earlier launch, that only reads done) sets to whether it ran.
+// On meshes small enough for slabs of one brick the launches and their
+// latency are what an iteration costs, and it takes two:
+//   apply   every workgroup sums the residual partials in the same order:
+//           beta = rz / rz_old and the convergence test; then the previous
+//           iteration's x += alpha p_old and p = z + beta p_old, formed where
+//           p is staged, q = A p, and per-slab partials of p.q   (heat.hip)
+//   update  every workgroup sums the partials of p.q in the same order:
+//           alpha = rz / p.q; then z -= alpha D^-1 q, the shared nodes of q
+//           summed from the face buffer; partials of r.z and r.r; iteration
+//           count, rz_old = rz
+// p alternates between two vectors, since neighbouring slabs read p_old where
+// a slab writes p.  32^3 cells, sine Heaviside: 28 us of kernels per iteration
+// in four launches, 22 in two (an implicit step with its adjoint 3.8 / 3.06
+// ms).  On slabs of four bricks the vectors' traffic, the same in both,
+// bounds them and is better spread by the plain vector kernels: 64^3 cells
+// 56 us in four launches, 58 in two (a solve 0.98 / 1.04 ms).
+//
+// Flags: a kernel whose workgroups write x or z reads no flag that its own
+// launch may write (its wavefronts would not agree).  In four launches done is
+// written by the combine pass (a breakdown: its workgroups that then skip their
+// nodes leave q incomplete, which no later step reads) and by the step kernel,
+// which tests `run` instead, set by the residual kernel.  In two, done is
+// written by the apply, on convergence, and by the poll's check; an update
+// kernel that sees it does nothing but set `ended`, for which the applies that
+// follow look (the apply before it has completed x).  A breakdown found by the
+// update kernel is breakdown = 1, for which the applies look too: the update
+// kernels behind them find the same partials and the same breakdown, and the
+// check sets done.
 // ---------------------------------------------------------------------------
 constexpr int CG_UNROLL = 4;
 
 __global__ void __launch_bounds__(VNT) cg_init_kernel(const double *__restrict__ b, const double *__restrict__ dinv,
                                                       double *__restrict__ x, double *__restrict__ r,
-                                                      double *__restrict__ p, int64_t n, int flexible, RedWS red)
+                                                      double *__restrict__ p, int64_t n, int form, RedWS red)
 {
     __shared__ double lds[2 * (VNT / 64)];
     double acc[2] = {0.0, 0.0};
@@ -764,15 +789,16 @@ __global__ void __launch_bounds__(VNT) cg_init_kernel(const double *__restrict__
     {
         const double bi = b[i];
         x[i] = 0.0;
-        if (!flexible) {
+        double pi = 0.0;
+        if (form != CG_FLEXIBLE) {
             const double zi = dinv ? dinv[i] * bi : bi;
             r[i] = zi; // the preconditioned CG keeps z = D^-1 r in place of r
-            p[i] = zi;
+            if (form == CG_PLAIN) pi = zi;
             acc[0] += bi * zi;
         } else {
             r[i] = bi;
-            p[i] = 0.0;
         }
+        p[i] = pi; // 0: the first direction is formed with beta = 0
         acc[1] += bi * bi;
     }
     grid_partials<2>(acc, red, lds);
@@ -799,19 +825,20 @@ __global__ void __launch_bounds__(FNT) cg_init_finalize_kernel(CGState *st, cons
         st->alpha = 0.0;
         st->beta = 0.0;
         st->pAp = 0.0;
+        st->ended = 0;
         st->done = (tot[1] == 0.0 || maxit <= 0) ? 1 : 0;
     }
 }
 
 hipError_t cg_init(CGState *st, const double *b, const double *dinv, double *x, double *r, double *p, int64_t n,
-                   double rtol, int maxit, int flexible, const RedWS *red, hipStream_t s)
+                   double rtol, int maxit, int form, const RedWS *red, hipStream_t s)
 {
     const unsigned nb = vec_blocks(n);
     if (red->capacity < 2 * nb) return hipErrorInvalidValue;
-    cg_init_kernel<<<nb, VNT, 0, s>>>(b, dinv, x, r, p, n, flexible, *red);
+    cg_init_kernel<<<nb, VNT, 0, s>>>(b, dinv, x, r, p, n, form, *red);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    cg_init_finalize_kernel<<<1, FNT, 0, s>>>(st, red->partials, nb, rtol, maxit, flexible);
+    cg_init_finalize_kernel<<<1, FNT, 0, s>>>(st, red->partials, nb, rtol, maxit, form == CG_FLEXIBLE);
     return hipGetLastError();
 }
 
@@ -989,6 +1016,225 @@ hipError_t cg_step(CGState *st, double *x, const double *z, double *p, int64_t n
                                               CG_STEP_BLOCKS);
     if (nb < 1) nb = 1;
     cg_step_kernel<<<nb, VNT, 0, s>>>(st, red->partials, cg_resid_blocks(n), x, z, p, n);
+    return hipGetLastError();
+}
+
+// Total of n partials, the same in every thread and workgroup.
+template <int NT> __device__ __forceinline__ double total_partials(const double *p, unsigned n, double *lds)
+{
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    for (unsigned b = threadIdx.x; b < n; b += 4 * NT) {
+#pragma unroll
+        for (unsigned k = 0; k < 4; ++k) t[k] += b + NT * k < n ? p[b + NT * k] : 0.0;
+    }
+    const double w = wave_sum((t[0] + t[1]) + (t[2] + t[3]));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x / 64] = w;
+    __syncthreads();
+    double r = 0.0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; ++k) r += lds[k];
+    __syncthreads();
+    return r;
+}
+
+// One workgroup takes a run of slabs (contiguous, as the apply numbers them,
+// so a slab's nodes are likely in the L2 of the XCD that wrote them), thread
+// (lx, ly) of a slab the nodes lz = lz0 + LZ k that the slab owns (all but those
+// on its shared high faces), the rest of a slab at the far end of the mesh
+// after them.  A node on a shared low face takes q from the face buffer: the
+// partials of the 2, 4 or 8 slabs that hold it, lower slab first in z, then y,
+// then x (the order of the combine pass, whose work this is).
+template <bool PC>
+__global__ void __launch_bounds__(VNT) cg_update_kernel(KMesh m, CGState *st, const double *__restrict__ ppart,
+                                                        unsigned nslabs, const double *__restrict__ face,
+                                                        const double *__restrict__ q, const double *__restrict__ p,
+                                                        const double *__restrict__ dinv, double *__restrict__ z,
+                                                        double *__restrict__ rpart)
+{
+    using SL = Slab<1>;
+    constexpr int RX = SL::RX, SP = SL::SP, NF = SL::NFACE, LZ = VNT / (RX * 2 * BB), K = 2 * BB / LZ;
+    static_assert(LZ * K == 2 * BB, "whole planes per step");
+    __shared__ double lds[2 * (VNT / 64)];
+    if (st->done) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->ended = 1;
+        return;
+    }
+    const int tid = (int)threadIdx.x, lx = tid % RX, ly = tid / RX % (2 * BB), lz0 = tid / (RX * 2 * BB);
+    const int nbx = (int)ceil_div(m.nx, SL::CX), nby = (int)ceil_div(m.ny, BB);
+    const int64_t dx = RX - NF, dy = (int64_t)SP * 2 * BB - (int64_t)nbx * NF,
+                  dz = (int64_t)SP * BP * 2 * BB - (int64_t)nbx * nby * NF;
+    const unsigned NXY = (unsigned)m.NX * (unsigned)m.NY;
+    double acc[2] = {0.0, 0.0};
+    // slabs per workgroup, and the workgroups that take one more
+    const unsigned li = (unsigned)Brick::xcd_index(), per = nslabs / gridDim.x, more = nslabs - per * gridDim.x;
+    const unsigned s0 = li * per + min(li, more), s1 = s0 + per + (li < more ? 1u : 0u);
+    double alpha = 0.0;
+    bool first = true;
+    for (unsigned s = s0; s < s1; ++s) {
+        const SL sl(m, tid, (int)s);
+        const int ex = 2 * sl.ncx, ey = 2 * sl.ncy, ez = 2 * sl.ncz;
+        const bool fx = sl.bx > 0, fy = sl.by > 0, fz = sl.bz > 0;
+        const unsigned dirf = sl.dirichlet_faces(m);
+        const int64_t o = node_index(m, 2 * sl.c0x, 2 * sl.c0y, 2 * sl.c0z);
+        const double *const fs = face + (int64_t)s * NF;
+        const double *const qs = q + o, *const ps = p + o, *const ds = PC ? dinv + o : nullptr;
+        double *const zs = z + o;
+        auto constrained = [&](int ax, int ay, int az) MF_INLINE -> bool { // identity rows: q = p
+            return ((sl.x_faces(ax) | sl.yz_faces(ay, az)) & dirf) != 0u;
+        };
+        auto update = [&](unsigned off, double qv, double zv, double dv) MF_INLINE {
+            if (PC) {
+                // the vector holds z = D^-1 r: z -= alpha D^-1 q, r = z / D^-1
+                const double zi = zv - alpha * (dv * qv);
+                zs[off] = zi;
+                const double ri = zi / dv;
+                acc[0] += ri * zi;
+                acc[1] += ri * ri;
+            } else {
+                const double ri = zv - alpha * qv;
+                zs[off] = ri;
+                acc[0] += ri * ri;
+                acc[1] += ri * ri;
+            }
+        };
+        // every read is issued before the first is used: per kind of node one
+        // branch around the reads of all steps
+        const bool okxy = lx <= ex && ly <= ey, sx = okxy && lx == 0 && fx, sy = okxy && ly == 0 && fy;
+        const bool sz = okxy && lz0 == 0 && fz; // of step 0
+        const unsigned off0 = (unsigned)lx + (unsigned)m.NX * (unsigned)ly;
+        const double *const f0 = fs + lx + SP * (ly + BP * lz0);
+        constexpr int FS = SP * BP * LZ; // from one step's slot to the next
+        double zv[K], dv[K], t0[K], tx[K], ty[K], txy[K], tz[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int lz = lz0 + LZ * k;
+            const bool ok = okxy && lz <= ez;
+            const unsigned off = ok ? off0 + NXY * (unsigned)lz : 0u;
+            zv[k] = zs[off];
+            if (PC) dv[k] = ds[off];
+            const double *const src = ok && (sx || sy || (k == 0 && sz)) ? f0 + FS * k : qs + off;
+            t0[k] = *(constrained(lx, ly, lz) ? ps + off : src);
+            tx[k] = ty[k] = txy[k] = 0.0;
+        }
+        if (sx) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) tx[k] = f0[FS * k + dx];
+        }
+        if (sy) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) ty[k] = f0[FS * k + dy];
+        }
+        if (sx && sy) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) txy[k] = f0[FS * k + dx + dy];
+        }
+        if (sz) {
+            tz[3] = f0[dz];
+            if (sx) tz[2] = f0[dz + dx];
+            if (sy) tz[1] = f0[dz + dy];
+            if (sx && sy) tz[0] = f0[dz + dx + dy];
+        }
+        if (first) { // with the first slab's reads in flight
+            first = false;
+            const double pAp = total_partials<VNT>(ppart, nslabs, lds);
+            const bool bad = !(pAp > 0.0) || !isfinite(pAp);
+            const double rz = st->rz;
+            alpha = rz / pAp;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                // no workgroup of this launch reads these
+                st->pAp = pAp;
+                st->alpha = bad ? 0.0 : alpha;
+                if (bad) {
+                    st->breakdown = 1;
+                } else {
+                    st->iter += 1;
+                    st->rz_old = rz;
+                }
+            }
+            if (bad) return;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int lz = lz0 + LZ * k;
+            const double zsum = k == 0 ? ((tz[0] + tz[1]) + tz[2]) + tz[3] : 0.0;
+            const double sum = (((zsum + txy[k]) + ty[k]) + tx[k]) + t0[k];
+            if (okxy && lz <= ez)
+                update(off0 + NXY * (unsigned)lz, constrained(lx, ly, lz) ? t0[k] : sum, zv[k], PC ? dv[k] : 1.0);
+        }
+        // the far end of the mesh: the owned nodes on the slab's high faces
+        const int ox = SL::owned_end(m.nx, sl.c0x, SL::CX), oy = SL::owned_end(m.ny, sl.c0y, BB),
+                  oz = SL::owned_end(m.nz, sl.c0z, BB);
+        const int wx = ox + 1, my = min(oy + 1, 2 * BB), mz = min(oz + 1, 2 * BB);
+        const int nz = oz == 2 * BB ? wx * (oy + 1) : 0, ny = oy == 2 * BB ? wx * mz : 0, nx = ox == RX ? my * mz : 0;
+        for (int j0 = tid; j0 < nz + ny + nx; j0 += VNT) {
+            int j = j0, ax, ay, az;
+            if (j < nz) {
+                az = 2 * BB;
+                ay = j / wx;
+                ax = j - wx * ay;
+            } else if ((j -= nz) < ny) {
+                ay = 2 * BB;
+                az = j / wx;
+                ax = j - wx * az;
+            } else {
+                j -= ny;
+                ax = RX;
+                az = j / my;
+                ay = j - my * az;
+            }
+            const unsigned off = (unsigned)ax + (unsigned)m.NX * (unsigned)ay + NXY * (unsigned)az;
+            const double zj = zs[off], dj = PC ? ds[off] : 1.0;
+            const bool con = constrained(ax, ay, az);
+            const bool jx = ax == 0 && fx && !con, jy = ay == 0 && fy && !con, jz = az == 0 && fz && !con;
+            const double *const g0 = fs + ax + SP * (ay + BP * az);
+            double t[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            t[7] = *(con ? ps + off : jx || jy || jz ? g0 : qs + off);
+            if (jx) t[6] = g0[dx];
+            if (jy) t[5] = g0[dy];
+            if (jx && jy) t[4] = g0[dx + dy];
+            if (jz) t[3] = g0[dz];
+            if (jz && jx) t[2] = g0[dz + dx];
+            if (jz && jy) t[1] = g0[dz + dy];
+            if (jx && jy && jz) t[0] = g0[dz + dx + dy];
+            update(off, ((((((t[0] + t[1]) + t[2]) + t[3]) + t[4]) + t[5]) + t[6]) + t[7], zj, dj);
+        }
+    }
+    grid_partials<2>(acc, RedWS{rpart, 0}, lds);
+}
+
+unsigned cg_update_blocks(unsigned nslabs) { return std::min(nslabs, CG_MAX_UPDATE); }
+
+hipError_t cg_update(const KMesh &m, CGState *st, unsigned nslabs, const double *ppart, const void *face,
+                     const double *q, const double *p, const double *dinv, double *z, double *rpart, hipStream_t s)
+{
+    const unsigned nb = cg_update_blocks(nslabs);
+    const double *fb = (const double *)face;
+    if (dinv) cg_update_kernel<true><<<nb, VNT, 0, s>>>(m, st, ppart, nslabs, fb, q, p, dinv, z, rpart);
+    else cg_update_kernel<false><<<nb, VNT, 0, s>>>(m, st, ppart, nslabs, fb, q, p, dinv, z, rpart);
+    return hipGetLastError();
+}
+
+__global__ void __launch_bounds__(VNT) cg_check_kernel(CGState *st, const double *__restrict__ rpart, unsigned nb)
+{
+    __shared__ double tot[2];
+    if (st->done) return; // the apply's own test
+    if (st->breakdown) { // by the update kernel: no update since the apply stored rr
+        if (threadIdx.x == 0) st->done = 1;
+        return;
+    }
+    if (st->iter == 0) return;
+    wave_set_sums<2>(rpart, nb, tot);
+    if (threadIdx.x == 0) {
+        const bool bad = !isfinite(tot[0]) || !isfinite(tot[1]);
+        st->rr = tot[1];
+        if (bad) st->breakdown = 2;
+        if (bad || tot[1] <= st->thresh2 || st->iter >= st->maxit) st->done = 1;
+    }
+}
+
+hipError_t cg_check(CGState *st, const double *rpart, unsigned nb, hipStream_t s)
+{
+    cg_check_kernel<<<1, VNT, 0, s>>>(st, rpart, nb);
     return hipGetLastError();
 }
 
