@@ -657,20 +657,22 @@ template <int W> __host__ __device__ inline int64_t n_slabs(const KMesh &m)
 // Slabs of four sub-bricks: where at least three of four sub-brick slots along
 // x hold cells (then their face buffer, 2673 slots, is no larger than the
 // 3 * 891 of as many bricks either), and from 1200 bricks on, where the four
-// wavefronts of a slab no longer leave CUs idle.  FP64 apply, W = 4 against
-// W = 1: 32^3 cells (512 bricks) 14.4 / 13.6 us, 40^3 17.7 / 16.0, 44^3 (1331)
-// 18.4 / 18.7, 48^3 19.2 / 20.2, 64^3 30.2 / 35.0, 112^3 136 / 183; with
-// sub-bricks left over: 53^3 (14 of 16) 26.8 / 25.4, 67^3 (17 of 20) 37.9 /
-// 44.8.  FP32: 40^3 15.9 / 14.8, 48^3 17.4 / 18.0, 128^3 127 / 169.
-// The heavier forms (a third staged field, coefficients per point, the sine
-// Heaviside, whose polynomial only some wavefronts of a slab evaluate) pay
-// more for a partly filled last round of slabs: convective transpose
-// 45x64x51 (624 slabs on 512 places) 35.4 / 33.8 us, 64^3 49.3 / 54.0;
-// coefficients per point FP32 48^3 19.0 / 18.0; sine 50x37x61 27.6 / 24.7,
-// 64^3 36.6 / 36.1.
+// wavefronts of a slab no longer leave CUs idle; up to 3200, where the slabs
+// fill at most one round and a half of the 512 that the CUs hold, only if more
+// than seven of eight slots hold cells.  FP64 apply, W = 4 against W = 1: 40^3
+// cells 17.7 / 16.0 us, 44^3 (1331 bricks) 18.5 / 19.3, 48^3 19.2 / 20.2, 53^3
+// (14 of 16 slots) 26.8 / 24.2, 56^3 27.4 / 25.5, 60^3 28.4 / 30.6, 64^3 30.1 /
+// 33.3, 70^3 (18 of 20) 41.7 / 50.7.  FP32: 40^3 15.9 / 15.0, 48^3 17.8 / 18.4,
+// 128^3 127 / 169.  The heavier forms (a third staged field, coefficients per
+// point, the sine Heaviside, whose polynomial only some wavefronts of a slab
+// evaluate) pay more for a partly filled last round of slabs, up to 3300
+// bricks: convective 56^3 41.8 / 36.1, 60^3 (3375) 45.6 / 48.7; three phases
+// 56^3 39.7 / 35.2, 60^3 41.0 / 41.6; sine 56^3 33.1 / 29.4, 64^3 36.6 / 36.1.
 inline bool use_wide_slabs(const KMesh &m, bool heavy)
 {
-    return n_bricks(m) >= (heavy ? 3600 : 1200) && (int)ceil_div(m.nx, BB) >= 3 * (int)ceil_div(m.nx, 4 * BB);
+    const int64_t nb = n_bricks(m);
+    const int used = (int)ceil_div(m.nx, BB), slots = 4 * (int)ceil_div(m.nx, 4 * BB);
+    return nb >= (heavy ? 3300 : 1200) && (nb < 3200 ? 8 * used > 7 * slots : 4 * used >= 3 * slots);
 }
 
 // LDS of W > 1 beside the staged fields: the sums on the sub-bricks' x-high
@@ -681,10 +683,20 @@ template <int W_, int R_ = (W_ == 1 ? 10 : 8 * W_ + 4)> struct Slab {
     static constexpr int W = W_, NT = W * BNT;
     static constexpr int RX = 2 * W * BB, SP = RX + 1; // nodes along x without and with the high face
     static constexpr int CX = W * BB;
-    static constexpr int NFACE = SP * BP * BP; // one slot per node, surface nodes used
+    // Face buffer: one slot per node, surface nodes used; the x-low face, the
+    // x-high face, then the rows without their ends, so that a combine pass
+    // reads the x faces contiguously too (with whole rows of 9 the 49 nodes of
+    // a brick's x face lay on as many lines: convective apply on 56^3 cells 38.5
+    // us, 36.1 so; plain FP64 on 77^3 53.4, 50.6).
+    static constexpr int NFACE = SP * BP * BP, ROWS = BP * BP;
+    static __device__ __forceinline__ constexpr int face_row(int lx) // slots from one row (ly + 9 lz) to the next
+    {
+        return lx == 0 || lx == SP - 1 ? 1 : SP - 2;
+    }
     static __device__ __forceinline__ constexpr int face_slot_of(int lx, int ly, int lz)
     {
-        return lx + SP * (ly + BP * lz);
+        const int start = lx == 0 ? 0 : lx == SP - 1 ? ROWS : 2 * ROWS + lx - 1;
+        return start + face_row(lx) * (ly + BP * lz);
     }
     // LDS layout of a staged field: node (lx, ly, lz) at lx + R ly + plane lz.
     // A wavefront gathers nodes (2tx + a, 2ty + b, 2tz + c): with R = 4 (mod
@@ -1021,18 +1033,18 @@ template <typename T, bool CG, typename SL>
 __device__ __forceinline__ void finish_nodes(const KMesh &m, const SL &br, T *__restrict__ y, T *__restrict__ face,
                                              T (&v)[SL::NV], T (&xv)[SL::NV], double &energy)
 {
-    constexpr int K = SL::STEPS, SP = SL::SP;
+    constexpr int K = SL::STEPS;
     T *const yb = y + node_index(m, 2 * br.c0x, 2 * br.c0y, 2 * br.c0z);
-    T *const fb = face + (int64_t)br.brick * SL::NFACE; // slot lx + SP row
-    const int lx = br.tid % SL::RX, r0 = br.tid / SL::RX;
-    T *const f0 = fb + lx + SP * r0, *const fe = fb + SL::RX + SP * br.tid;
+    T *const fb = face + (int64_t)br.brick * SL::NFACE;
+    const int lx = br.tid % SL::RX, r0 = br.tid / SL::RX, fstep = SL::RPS * SL::face_row(lx);
+    T *const f0 = fb + SL::face_slot_of(lx, r0, 0), *const fe = fb + SL::face_slot_of(SL::RX, br.tid, 0); // row r: ly = r, lz = 0
     const unsigned shf = br.shared_faces(m), dirf = br.dirichlet_faces(m);
     if (shf == 63u) { // neighbours on all sides
         // steps 0, 9 and 10 are the two z faces; of step k in between the
         // rows r0 = k (ly = 0) and k - 1 (ly = 8) lie on the y faces
         br.template for_rows<T>(m, [&](auto kc, int, unsigned off, int, int, bool ok) MF_INLINE {
             constexpr int k = decltype(kc)::value;
-            T *d = f0 + k * (SL::RPS * SP);
+            T *d = f0 + k * fstep;
             if constexpr (k >= 1 && k <= 8) d = (lx == 0 || r0 == k || r0 == k - 1) ? d : yb + off;
             if constexpr (CG) energy += ok ? (double)xv[k] * (double)v[k] : 0.0;
             if (k < K - 1 || ok) *d = v[k];
@@ -1040,7 +1052,7 @@ __device__ __forceinline__ void finish_nodes(const KMesh &m, const SL &br, T *__
         br.template for_edge<T>(m, [&](auto kc, int, unsigned, int, int, bool ok) MF_INLINE {
             constexpr int k = decltype(kc)::value;
             if constexpr (CG) energy += ok ? (double)xv[K + k] * (double)v[K + k] : 0.0;
-            if (ok) fe[k * (SL::NT * SP)] = v[K + k];
+            if (ok) fe[k * SL::NT] = v[K + k];
         });
         return;
     }
@@ -1061,11 +1073,11 @@ __device__ __forceinline__ void finish_nodes(const KMesh &m, const SL &br, T *__
     const unsigned fx = br.x_faces(lx), fxe = br.x_faces(SL::RX);
     br.template for_rows<T>(m, [&](auto kc, int, unsigned off, int ly, int lz, bool ok) MF_INLINE {
         constexpr int k = decltype(kc)::value;
-        finish(T(v[k]), T(xv[k]), f0 + k * (SL::RPS * SP), off, fx, lx <= ex, ly, lz, ok);
+        finish(T(v[k]), T(xv[k]), f0 + k * fstep, off, fx, lx <= ex, ly, lz, ok);
     });
     br.template for_edge<T>(m, [&](auto kc, int, unsigned off, int ly, int lz, bool ok) MF_INLINE {
         constexpr int k = decltype(kc)::value;
-        finish(T(v[K + k]), T(xv[K + k]), fe + k * (SL::NT * SP), off, fxe, SL::RX <= ex, ly, lz, ok);
+        finish(T(v[K + k]), T(xv[K + k]), fe + k * SL::NT, off, fxe, SL::RX <= ex, ly, lz, ok);
     });
 }
 

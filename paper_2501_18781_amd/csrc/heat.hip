@@ -647,7 +647,7 @@ hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x
 unsigned heat_cg_slabs(const KMesh &m, const HeatArgs &a)
 {
     const int64_t nb = n_bricks(m);
-    return wide_slabs(m, a) || nb >= 3600 ? 0u : (unsigned)nb;
+    return wide_slabs(m, a) || nb >= 3300 ? 0u : (unsigned)nb;
 }
 
 hipError_t heat_cg_apply(const KMesh &m, const HeatArgs &a, const CGDir &dir, double *q, void *face, CGState *cg,

@@ -1052,7 +1052,7 @@ __global__ void __launch_bounds__(VNT) cg_update_kernel(KMesh m, CGState *st, co
                                                         double *__restrict__ rpart)
 {
     using SL = Slab<1>;
-    constexpr int RX = SL::RX, SP = SL::SP, NF = SL::NFACE, LZ = VNT / (RX * 2 * BB), K = 2 * BB / LZ;
+    constexpr int RX = SL::RX, NF = SL::NFACE, LZ = VNT / (RX * 2 * BB), K = 2 * BB / LZ;
     static_assert(LZ * K == 2 * BB, "whole planes per step");
     __shared__ double lds[2 * (VNT / 64)];
     if (st->done) {
@@ -1061,8 +1061,12 @@ __global__ void __launch_bounds__(VNT) cg_update_kernel(KMesh m, CGState *st, co
     }
     const int tid = (int)threadIdx.x, lx = tid % RX, ly = tid / RX % (2 * BB), lz0 = tid / (RX * 2 * BB);
     const int nbx = (int)ceil_div(m.nx, SL::CX), nby = (int)ceil_div(m.ny, BB);
-    const int64_t dx = RX - NF, dy = (int64_t)SP * 2 * BB - (int64_t)nbx * NF,
-                  dz = (int64_t)SP * BP * 2 * BB - (int64_t)nbx * nby * NF;
+    // from a low face's slot to the same node's in the lower slab: across x
+    // (lx = 0), y and z (row is the slots from one row of nodes to the next)
+    const int64_t ny0 = (int64_t)nbx * NF, nz0 = (int64_t)nbx * nby * NF;
+    const int64_t dx = SL::ROWS - NF;
+    const int row = SL::face_row(lx);
+    const int64_t dy = 2 * BB * row - ny0, dz = BP * 2 * BB * row - nz0;
     const unsigned NXY = (unsigned)m.NX * (unsigned)m.NY;
     double acc[2] = {0.0, 0.0};
     // slabs per workgroup, and the workgroups that take one more
@@ -1102,8 +1106,8 @@ __global__ void __launch_bounds__(VNT) cg_update_kernel(KMesh m, CGState *st, co
         const bool okxy = lx <= ex && ly <= ey, sx = okxy && lx == 0 && fx, sy = okxy && ly == 0 && fy;
         const bool sz = okxy && lz0 == 0 && fz; // of step 0
         const unsigned off0 = (unsigned)lx + (unsigned)m.NX * (unsigned)ly;
-        const double *const f0 = fs + lx + SP * (ly + BP * lz0);
-        constexpr int FS = SP * BP * LZ; // from one step's slot to the next
+        const double *const f0 = fs + SL::face_slot_of(lx, ly, lz0);
+        const int FS = BP * LZ * row; // from one step's slot to the next
         double zv[K], dv[K], t0[K], tx[K], ty[K], txy[K], tz[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -1186,16 +1190,17 @@ __global__ void __launch_bounds__(VNT) cg_update_kernel(KMesh m, CGState *st, co
             const double zj = zs[off], dj = PC ? ds[off] : 1.0;
             const bool con = constrained(ax, ay, az);
             const bool jx = ax == 0 && fx && !con, jy = ay == 0 && fy && !con, jz = az == 0 && fz && !con;
-            const double *const g0 = fs + ax + SP * (ay + BP * az);
+            const double *const g0 = fs + SL::face_slot_of(ax, ay, az);
+            const int64_t jdy = 2 * BB * SL::face_row(ax) - ny0, jdz = BP * 2 * BB * SL::face_row(ax) - nz0;
             double t[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             t[7] = *(con ? ps + off : jx || jy || jz ? g0 : qs + off);
             if (jx) t[6] = g0[dx];
-            if (jy) t[5] = g0[dy];
-            if (jx && jy) t[4] = g0[dx + dy];
-            if (jz) t[3] = g0[dz];
-            if (jz && jx) t[2] = g0[dz + dx];
-            if (jz && jy) t[1] = g0[dz + dy];
-            if (jx && jy && jz) t[0] = g0[dz + dx + dy];
+            if (jy) t[5] = g0[jdy];
+            if (jx && jy) t[4] = g0[dx + jdy];
+            if (jz) t[3] = g0[jdz];
+            if (jz && jx) t[2] = g0[jdz + dx];
+            if (jz && jy) t[1] = g0[jdz + jdy];
+            if (jx && jy && jz) t[0] = g0[jdz + dx + jdy];
             update(off, ((((((t[0] + t[1]) + t[2]) + t[3]) + t[4]) + t[5]) + t[6]) + t[7], zj, dj);
         }
     }
