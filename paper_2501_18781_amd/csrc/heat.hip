@@ -339,10 +339,11 @@ __device__ __forceinline__ void heat_conv_cell_apply(const BR &br, const KMesh &
 // W > 1 a third region for the z exchange of the node sums (with W = 1 that
 // overlays phi), which holds the frozen temperature or one velocity
 // component before.
+// TILE: an overlapping tile (brick.hpp) in place of a slab of one brick.
 // CG: the epilogue sums p.Ap.  DIR (with CG): x is p = z + beta p_old, formed in
 // the staging from the previous iteration's residual partials (CGDir); once
 // converged only x is completed.
-template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W, bool DIR>
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W, bool DIR, bool TILE>
 __device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &a, const T *__restrict__ x,
                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
                                                 double *partials, const CGDir &dir)
@@ -350,7 +351,8 @@ __device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &
     static_assert(!DIR || (CG && W == 1 && std::is_same<T, double>::value), "the direction update is CG's");
     static_assert(CONV == 0 || (std::is_same<T, double>::value && MODE == 0 && !CG), "convective form: FP64 only");
     static_assert(MODE != 2 || std::is_same<T, double>::value, "three-phase coefficients: FP64 only");
-    using SL = Slab<W>;
+    static_assert(!TILE || (!CG && W == 1), "a tile computes nodes that it does not own");
+    using SL = std::conditional_t<TILE, Tile, Slab<W>>;
     constexpr int NF = SL::template field<T>(), XCH = W > 1 ? 9 * SL::NT : 0;
     static_assert(NF >= 9 * BNT, "with W = 1 the z exchange overlays phi");
     constexpr int THIRD = (MODE == 2 || CONV != 0) && NF > XCH ? NF : XCH;
@@ -458,7 +460,8 @@ __device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &
 #pragma unroll
         for (int k = 0; k < SL::NV; ++k) xv[k] = T(0);
     }
-    finish_nodes<T, CG>(m, br, y, face, v, xv, energy);
+    if constexpr (TILE) finish_tile<T>(m, br, y, v, xv);
+    else finish_nodes<T, CG>(m, br, y, face, v, xv, energy);
     if (CG) {
         // one partial per slab; the alpha kernel sums them in slab order
         double tot = wave_total(energy);
@@ -478,14 +481,20 @@ __global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatAr
                                                                  T *__restrict__ y, T *__restrict__ face, CGState *cg,
                                                                  RedWS red)
 {
-    heat_apply_slab<T, MODE, HK, CG, CONV, ISO, W, false>(m, a, x, y, face, cg, red.partials, CGDir{});
+    heat_apply_slab<T, MODE, HK, CG, CONV, ISO, W, false, false>(m, a, x, y, face, cg, red.partials, CGDir{});
+}
+
+template <typename T, int MODE, int HK, int CONV, bool ISO>
+__global__ void __launch_bounds__(BNT) heat_tile_kernel(KMesh m, HeatArgs a, const T *__restrict__ x, T *__restrict__ y)
+{
+    heat_apply_slab<T, MODE, HK, false, CONV, ISO, 1, false, true>(m, a, x, y, nullptr, nullptr, nullptr, CGDir{});
 }
 
 template <int MODE, int HK, bool ISO>
 __global__ void __launch_bounds__(BNT) heat_cg_apply_kernel(KMesh m, HeatArgs a, CGDir dir, double *__restrict__ q,
                                                             double *__restrict__ face, CGState *cg, double *ppart)
 {
-    heat_apply_slab<double, MODE, HK, true, 0, ISO, 1, true>(m, a, nullptr, q, face, cg, ppart, dir);
+    heat_apply_slab<double, MODE, HK, true, 0, ISO, 1, true, false>(m, a, nullptr, q, face, cg, ppart, dir);
 }
 
 // alpha = rz / p.Ap from the partials of a CG-mode apply, by one workgroup.
@@ -569,6 +578,15 @@ static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void
     return hipGetLastError();
 }
 
+// Overlapping tiles up to two on each of the 1024 SIMDs, what their registers
+// allow at once; one on each for the three-phase coefficients, whose two
+// staged fields and 27 divisions weigh most.  Tiles against slabs: 30^3 cells
+// (1000 tiles) 8.8 / 12.8 us, FP32 8.4 / 12.6, convective 13.2 / 16.1, three
+// phases 12.8 / 16.5; 37^3 (1728) 11.5 / 15.2, FP32 10.1 / 14.0, sine 15.6 /
+// 17.0, per point 13.4 / 16.5, convective 18.0 / 18.4, three phases 33^3 (1331)
+// 18.4 / 18.0.
+static bool use_tiles(const KMesh &m, const HeatArgs &a) { return Tile::count(m) <= (a.mode == 2 ? 1024 : 2048); }
+
 static bool wide_slabs(const KMesh &m, const HeatArgs &a)
 {
     return use_wide_slabs(m, a.conv != 0 || a.mode != 0 || a.hkind != 0);
@@ -578,6 +596,17 @@ template <typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
 static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face,
                                     CGState *cg, const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
+    if constexpr (!CGF) {
+        if (use_tiles(m, a)) { // one launch; face is not used
+            const unsigned nt = (unsigned)Tile::count(m);
+            if (ev0)
+                hipExtLaunchKernelGGL(heat_tile_kernel<T, MODE, HK, CV, ISO>, dim3(nt), dim3(BNT), 0, s, ev0, ev1, 0, m, a,
+                                      (const T *)x, (T *)y);
+            else
+                heat_tile_kernel<T, MODE, HK, CV, ISO><<<nt, BNT, 0, s>>>(m, a, (const T *)x, (T *)y);
+            return hipGetLastError();
+        }
+    }
     if (wide_slabs(m, a)) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
     return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 1>(m, a, x, y, face, cg, r, s, ev0, ev1);
 }

@@ -84,7 +84,8 @@ struct KTiming {
 };
 
 // ---- heat (heat.hip) ----
-// y = A x in two launches (bricks, then the shared-face combine); `face` is
+// y = A x in two launches (slabs, then the shared-face combine), on small
+// meshes in one (overlapping tiles, without CG); `face` is
 // a workspace of face_buffer_elems(m) elements of the operator's type.  With
 // cg != nullptr (FP64 only) the apply also forms p.Ap from per-brick
 // partials and a third, single-workgroup launch sets alpha = rz / p.Ap.
