@@ -52,7 +52,7 @@ __device__ __forceinline__ double solid_fraction(const OseenArgs &a, double T)
 }
 __device__ __forceinline__ double solid_indicator(double fs) { return fs * fs * (3.0 - 2.0 * fs); }
 
-// Gauss-point fields shared by the brick's three wavefronts are kept in LDS
+// Gauss-point fields shared by the brick's wavefronts are kept in LDS
 // as [q][cell] (27 x 64 doubles each): a lane reads its own cell's column,
 // consecutive lanes in consecutive banks.
 constexpr int GQ = 27 * BNT; // doubles of one shared Gauss-point field
