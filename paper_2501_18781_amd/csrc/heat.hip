@@ -156,14 +156,6 @@ __device__ __forceinline__ void heat_cell_coeffs3(const BR &br, const KMesh &m, 
     }
 }
 
-// Sum over the wavefront, identical in every lane.
-__device__ __forceinline__ double wave_total(double v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return __shfl(v, 0, 64);
-}
-
 // y_e = A_e x_e on one cell, in place on u (27 nodal values in, 27 out).
 template <typename T>
 __device__ __forceinline__ void heat_cell_apply(T *u, const T *cm, const T *ck, T ihx, T ihy, T ihz)

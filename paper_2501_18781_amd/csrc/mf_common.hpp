@@ -530,6 +530,14 @@ __device__ __forceinline__ void write_partials(const double *v, double *partials
     }
 }
 
+// Sum over the wavefront, identical in every lane.
+__device__ __forceinline__ double wave_total(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    return __shfl(v, 0, 64);
+}
+
 // One lane's share of a set of n partials, entries lane, lane + 64, ..., eight
 // loads in flight.
 __device__ __forceinline__ double lane_partials(const double *p, unsigned n, unsigned lane)

@@ -1228,7 +1228,14 @@ __global__ void __launch_bounds__(VNT) cg_check_kernel(CGState *st, const double
         return;
     }
     if (st->iter == 0) return;
-    wave_set_sums<2>(rpart, nb, tot);
+    // a wavefront per set, summed in the order of the apply's own test: at the
+    // threshold both have to decide alike
+    const unsigned w = threadIdx.x / 64;
+    if (w < 2) {
+        const double s = wave_total(lane_partials(rpart + w * nb, nb, threadIdx.x & 63));
+        if ((threadIdx.x & 63) == 0) tot[w] = s;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
         const bool bad = !isfinite(tot[0]) || !isfinite(tot[1]);
         st->rr = tot[1];
