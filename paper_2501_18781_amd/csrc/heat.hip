@@ -535,15 +535,9 @@ __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__r
     combine_slabs<T, W>(m, face, x, y);
 }
 
-int64_t face_buffer_elems(const KMesh &m)
-{
-    // the larger of the bricks' slots (those of any slab layout are fewer)
-    // and 1683 per 4x4x8 cells, which is what mf_operator_apply_noalloc's
-    // fixed scratch admits
-    const int64_t b4 = n_bricks(m) * BFACE;
-    const int64_t b8 = (int64_t)ceil_div(m.nx, BB) * ceil_div(m.ny, BB) * ceil_div(m.nz, 8) * 1683;
-    return b4 > b8 ? b4 : b8;
-}
+// A brick's slots; those of any slab layout are at most as many (use_wide_slabs,
+// Slab::NFACE).  This is the bound that mf.h states for mf_operator_apply_noalloc.
+int64_t face_buffer_elems(const KMesh &m) { return n_bricks(m) * BFACE; }
 
 // One apply: the slab kernel, then the combine pass of its shared nodes
 // (with CG, alpha from the slabs' partials of p.Ap).  With timing on, the
