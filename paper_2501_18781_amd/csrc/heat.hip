@@ -1052,11 +1052,12 @@ hipError_t heat_qp_coeffs(const KMesh &m, const HeatArgs &a, double *kq, double 
 //   drc_q = -alpha_m W_q lam dT
 //   dphi_j = sum_q N_j(x_q) H'(phi_q) [(k_l - k_g) dk_q + (rc_l - rc_g) drc_q]
 // ---------------------------------------------------------------------------
-template <int HK>
-__global__ void __launch_bounds__(BNT) __attribute__((amdgpu_waves_per_eu(2, 2))) heat_grad_kernel(KMesh m, HeatArgs a, const double *__restrict__ T,
-                                                        const double *__restrict__ dT, const double *__restrict__ lam,
-                                                        double *__restrict__ dk, double *__restrict__ drc,
-                                                        double *__restrict__ dphi, double *__restrict__ face)
+// WPE: wavefronts per SIMD.  Two of them need two registers spilled.
+template <int HK, int WPE>
+__global__ void __launch_bounds__(BNT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
+heat_grad_kernel(KMesh m, HeatArgs a, const double *__restrict__ T, const double *__restrict__ dT,
+                 const double *__restrict__ lam, double *__restrict__ dk, double *__restrict__ drc,
+                 double *__restrict__ dphi, double *__restrict__ face)
 {
     constexpr int NF = 4;
     constexpr int NB = lds_field<double>();
@@ -1135,10 +1136,21 @@ hipError_t heat_grad(const KMesh &m, const HeatArgs &a, const double *T, const d
 {
     const unsigned nb = (unsigned)n_bricks(m);
     if (dphi && !face) return hipErrorInvalidValue;
-    if (a.mode == 0 && a.hkind)
-        heat_grad_kernel<1><<<nb, BNT, 0, s>>>(m, a, T, dT, lam, dk, drc, dphi, (double *)face);
-    else
-        heat_grad_kernel<0><<<nb, BNT, 0, s>>>(m, a, T, dT, lam, dk, drc, dphi, (double *)face);
+    // Two wavefronts per SIMD once there are more bricks than SIMDs, and with the
+    // per-point outputs only up to 4900 bricks: their stores, 8 bytes of every
+    // 216, fill whole lines in the L2 only while few wavefronts are in flight.
+    // dphi alone, one / two per SIMD: 24^3 cells 14.6 / 14.8 us, 42^3 26.3 / 22.1,
+    // 112^3 270 / 243; all three outputs: 24^3 16.7 / 17.5, 44^3 57.2 / 49.8, 60^3 97.3 /
+    // 94.1, 64^3 106 / 105, 70^3 160 / 169, 112^3 588 / 667 (sine form 582 / 640).
+    const bool two = nb > 1024u && !((dk || drc) && nb > 4900u);
+    auto launch = [&](auto HK) {
+        if (two)
+            heat_grad_kernel<decltype(HK)::value, 2><<<nb, BNT, 0, s>>>(m, a, T, dT, lam, dk, drc, dphi, (double *)face);
+        else
+            heat_grad_kernel<decltype(HK)::value, 1><<<nb, BNT, 0, s>>>(m, a, T, dT, lam, dk, drc, dphi, (double *)face);
+    };
+    if (a.mode == 0 && a.hkind) launch(std::integral_constant<int, 1>{});
+    else launch(std::integral_constant<int, 0>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !dphi || a.mode != 0) return e;
     // the level-set gradient sums over Dirichlet nodes too (DMODE 0)
