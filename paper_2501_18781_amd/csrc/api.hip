@@ -62,7 +62,8 @@ mf_status mesh_to_kmesh(mf_ctx *c, const mf_mesh *mesh, KMesh *out, int64_t *n_n
     k.loz = mesh->lo[2];
     k.rbx = udiv_reciprocal((unsigned)(k.nx + 3) / 4);
     k.rby = udiv_reciprocal((unsigned)(k.ny + 3) / 4);
-    k.rsx = udiv_reciprocal((unsigned)(k.nx + 15) / 16);
+    k.rs2 = udiv_reciprocal((unsigned)(k.nx + 7) / 8);
+    k.rs4 = udiv_reciprocal((unsigned)(k.nx + 15) / 16);
     *out = k;
     if (n_nodes) *n_nodes = nn;
     if (n_cells) *n_cells = nc;

@@ -632,7 +632,7 @@ __device__ __forceinline__ void combine_brick_visit(const KMesh &m, int brick, i
 // 25500 now).  A slab's rows are 33 nodes; it shares three quarters of the
 // nodes that four bricks share with their neighbours, and a quarter of those
 // on planes across x, which the combine pass can only write one by one.
-// W = 1 spreads a small mesh over four times the CUs.
+// W = 1 spreads a small mesh over four times the CUs; W = 2 is between them.
 // ---------------------------------------------------------------------------
 
 // A visitor whose arrays must stay in registers has to be inlined.
@@ -724,7 +724,7 @@ template <int W_, int R_ = (W_ == 1 ? 10 : 8 * W_ + 4)> struct Slab {
     __device__ __forceinline__ Slab(const KMesh &m, int tid_, int b) : brick(b), tid(tid_)
     {
         const int nbx = (int)ceil_div(m.nx, CX), nby = (int)ceil_div(m.ny, BB);
-        const int q = (int)udiv((unsigned)brick, (unsigned)nbx, W == 1 ? m.rbx : m.rsx);
+        const int q = (int)udiv((unsigned)brick, (unsigned)nbx, W == 1 ? m.rbx : W == 2 ? m.rs2 : m.rs4);
         bx = brick - q * nbx;
         bz = (int)udiv((unsigned)q, (unsigned)nby, m.rby);
         by = q - bz * nby;

@@ -578,6 +578,28 @@ static bool wide_slabs(const KMesh &m, const HeatArgs &a)
     return use_wide_slabs(m, a.conv != 0 || a.mode != 0 || a.hkind != 0);
 }
 
+// Sub-bricks per slab of the FP32 applies.  A brick's FP32 rows of 36 bytes use
+// little of a 128-byte line, and four wavefronts fit a SIMD, so two sub-bricks
+// are better than one from the first mesh that tiles leave, wherever their
+// slots fit the face buffer (not with one or three bricks along x); four where
+// the fields outgrow the last-level cache, if they waste few slots.  One / two
+// / four sub-bricks, and the 4x4x8-cell bricks that were here before slabs:
+// 38^3 cells 14.5 / 13.7 / 15.8 us (14.4), 52^3 20.4 / 17.7 / 19.2 (19.2),
+// 20x80x80 18.8 / 17.8 / 20.3 (17.6), 64^3 26.6 / 23.3 / 23.2 (25.2), 88^3 45.1 /
+// 40.0 / 41.7 (47.6), 128^3 158 / 120 / 108 (155), 36x200x200 (9 of 12 slots) 80.3
+// / 77.8 / 85.6 (84.2); per point 52^3 20.7 / 18.3 / 20.8 (19.9).  The sine form,
+// whose polynomial only some wavefronts evaluate, is better in single bricks
+// while each has a SIMD of its own (38^3 17.2 / 18.3, 44^3 20.1 / 18.9) and where
+// slots stay empty (20x80x80, 5 of 6: 22.1 / 23.6).
+static int slab_width_fp32(const KMesh &m, const HeatArgs &a)
+{
+    const int64_t nb = n_bricks(m);
+    const int used = (int)ceil_div(m.nx, BB), slots = 4 * (int)ceil_div(m.nx, 4 * BB);
+    if (nb >= 13000 && 8 * used > 7 * slots) return 4;
+    const bool sine = a.mode == 0 && a.hkind;
+    return used == 1 || used == 3 || (sine && (nb <= 1024 || used == 5)) ? 1 : 2;
+}
+
 template <typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
 static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face,
                                     CGState *cg, const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
@@ -593,7 +615,13 @@ static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const voi
             return hipGetLastError();
         }
     }
-    if (wide_slabs(m, a)) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
+    if constexpr (sizeof(T) == 4) {
+        const int w = slab_width_fp32(m, a);
+        if (w == 4) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
+        if (w == 2) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 2>(m, a, x, y, face, cg, r, s, ev0, ev1);
+    } else if (wide_slabs(m, a)) {
+        return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
+    }
     return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 1>(m, a, x, y, face, cg, r, s, ev0, ev1);
 }
 

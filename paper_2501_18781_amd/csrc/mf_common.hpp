@@ -34,8 +34,8 @@ struct KMesh {
     double hx, hy, hz;  // cell edges
     double lox, loy, loz;
     // floor(2^32 / d) (all ones for d = 1) of the divisors of a brick's index:
-    // bricks along x and y, slabs along x (see udiv)
-    unsigned rbx, rby, rsx;
+    // bricks along x and y, slabs of two and of four along x (see udiv)
+    unsigned rbx, rby, rs2, rs4;
 };
 
 // n / d for a uniform d with r = floor(2^32 / d): the product's high word is
