@@ -552,7 +552,7 @@ mf_status cg_solve(mf_ctx *c, const mf_operator *op, int precond, const double *
         HIPCHK(c, heat_diagonal(c->km, ha, 0, dinv, c->face, s, true));
     }
     RedWS red = redws(c);
-    const unsigned ns = heat_cg_slabs(c->km, ha); // 0: four launches per iteration, else two (see vec.hip)
+    const unsigned ns = heat_cg_slabs(c->km); // 0: four launches per iteration, else two (see vec.hip)
     const bool two = ns != 0;
     HIPCHK(c, cg_init(c->cg, b, dinv, x, r, p, n, rtol, maxit, two ? CG_TWO_LAUNCH : CG_PLAIN, &red, s));
     // Iterations are launched in batches, each followed by a copy of the

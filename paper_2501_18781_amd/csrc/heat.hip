@@ -685,18 +685,23 @@ hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x
     }
 }
 
-// Slabs of one brick, and few enough of them (an x extent that leaves slabs of
-// four half empty is no bound) for every update workgroup to sum their partials.
-unsigned heat_cg_slabs(const KMesh &m, const HeatArgs &a)
+// Two launches per CG iteration up to 1500 bricks: the direction's staging reads
+// two vectors more and writes two, at the one or two wavefronts per SIMD that the
+// apply's registers allow, which costs more than two launches once there are more
+// bricks than that.  40 iterations, two / four launches: 38^3 cells (1000 bricks)
+// 1.05 / 1.25 ms, 41^3 (1331) 1.33 / 1.42, 5x300x40 (1500) 1.30 / 1.42, 48^3 (1728) 1.64 /
+// 1.60, 52^3 (2197) 2.04 / 1.81, 56^3 (2744) 2.27 / 2.04; per point 44^3 (1331) 1.53 / 1.62,
+// 56^3 2.52 / 2.21; three phases 42^3 (1331) 1.65 / 1.73, 56^3 2.69 / 2.44.
+unsigned heat_cg_slabs(const KMesh &m)
 {
     const int64_t nb = n_bricks(m);
-    return wide_slabs(m, a) || nb >= 3300 ? 0u : (unsigned)nb;
+    return nb <= 1500 ? (unsigned)nb : 0u;
 }
 
 hipError_t heat_cg_apply(const KMesh &m, const HeatArgs &a, const CGDir &dir, double *q, void *face, CGState *cg,
                          double *ppart, hipStream_t s)
 {
-    const unsigned ns = heat_cg_slabs(m, a);
+    const unsigned ns = heat_cg_slabs(m);
     if (!face || a.conv || ns == 0) return hipErrorInvalidValue;
     const int hk = a.mode == 1 ? 0 : (a.hkind ? 1 : 0);
     const bool iso = m.hx == m.hy && m.hy == m.hz;

@@ -107,7 +107,7 @@ struct CGDir {
 hipError_t heat_cg_apply(const KMesh &m, const HeatArgs &a, const CGDir &dir, double *q, void *face, CGState *cg,
                          double *ppart, hipStream_t s);
 // The slabs of heat_cg_apply, or 0 where a CG iteration in four launches is better.
-unsigned heat_cg_slabs(const KMesh &m, const HeatArgs &a);
+unsigned heat_cg_slabs(const KMesh &m);
 hipError_t heat_qp_coeffs(const KMesh &m, const HeatArgs &a, double *kq, double *rcq, hipStream_t s);
 // Whole FP64 Jacobi-CG solve (x0 = 0) in one single-workgroup launch, for a
 // LEVELSET-mode operator on a mesh of at most 4 cells per direction; b and x

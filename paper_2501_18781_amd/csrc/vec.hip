@@ -748,8 +748,8 @@ hipError_t block3_apply(const double *B, const double *x, double *y, int64_t nn,
 // Nine vector passes per iteration (without a preconditioner z = r).
 // Each thread keeps CG_UNROLL elements of its grid-stride sequence in flight.
 //
-// On meshes small enough for slabs of one brick the launches and their
-// latency are what an iteration costs, and it takes two:
+// On small meshes (heat_cg_slabs) the launches and their latency are what an
+// iteration costs, and it takes two, on slabs of one brick:
 //   apply   every workgroup sums the residual partials in the same order:
 //           beta = rz / rz_old and the convergence test; then the previous
 //           iteration's x += alpha p_old and p = z + beta p_old, formed where
@@ -761,9 +761,9 @@ hipError_t block3_apply(const double *B, const double *x, double *y, int64_t nn,
 // p alternates between two vectors, since neighbouring slabs read p_old where
 // a slab writes p.  32^3 cells, sine Heaviside: 28 us of kernels per iteration
 // in four launches, 22 in two (an implicit step with its adjoint 3.8 / 3.06
-// ms).  On slabs of four bricks the vectors' traffic, the same in both,
-// bounds them and is better spread by the plain vector kernels: 64^3 cells
-// 56 us in four launches, 58 in two (a solve 0.98 / 1.04 ms).
+// ms).  On larger meshes the vectors' traffic, the same in both, bounds them and
+// is better spread by the plain vector kernels: 56^3 cells 50 us per iteration in
+// four launches, 57 in two.
 //
 // Flags: a kernel whose workgroups write x or z reads no flag that its own
 // launch may write (its wavefronts would not agree).  In four launches done is
