@@ -654,27 +654,6 @@ template <int W> __host__ __device__ inline int64_t n_slabs(const KMesh &m)
     return (int64_t)ceil_div(m.nx, W * BB) * ceil_div(m.ny, BB) * ceil_div(m.nz, BB);
 }
 
-// Slabs of four sub-bricks: where at least three of four sub-brick slots along
-// x hold cells (then their face buffer, 2673 slots, is no larger than the
-// 3 * 891 of as many bricks either), and from 1200 bricks on, where the four
-// wavefronts of a slab no longer leave CUs idle; up to 3200, where the slabs
-// fill at most one round and a half of the 512 that the CUs hold, only if more
-// than seven of eight slots hold cells.  FP64 apply, W = 4 against W = 1: 40^3
-// cells 17.7 / 16.0 us, 44^3 (1331 bricks) 18.5 / 19.3, 48^3 19.2 / 20.2, 53^3
-// (14 of 16 slots) 26.8 / 24.2, 56^3 27.4 / 25.5, 60^3 28.4 / 30.6, 64^3 30.1 /
-// 33.3, 70^3 (18 of 20) 41.7 / 50.7.  FP32: 40^3 15.9 / 15.0, 48^3 17.8 / 18.4,
-// 128^3 127 / 169.  The heavier forms (a third staged field, coefficients per
-// point, the sine Heaviside, whose polynomial only some wavefronts of a slab
-// evaluate) pay more for a partly filled last round of slabs, up to 3300
-// bricks: convective 56^3 41.8 / 36.1, 60^3 (3375) 45.6 / 48.7; three phases
-// 56^3 39.7 / 35.2, 60^3 41.0 / 41.6; sine 56^3 33.1 / 29.4, 64^3 36.6 / 36.1.
-inline bool use_wide_slabs(const KMesh &m, bool heavy)
-{
-    const int64_t nb = n_bricks(m);
-    const int used = (int)ceil_div(m.nx, BB), slots = 4 * (int)ceil_div(m.nx, 4 * BB);
-    return nb >= (heavy ? 3300 : 1200) && (nb < 3200 ? 8 * used > 7 * slots : 4 * used >= 3 * slots);
-}
-
 // LDS of W > 1 beside the staged fields: the sums on the sub-bricks' x-high
 // faces (81 each; read in whole steps of rows, hence the padding).
 template <int W> __host__ __device__ constexpr int slab_xhi() { return W > 1 ? 81 * (W - 1) + 8 : 0; }

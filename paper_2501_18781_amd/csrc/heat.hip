@@ -535,7 +535,7 @@ __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__r
     combine_slabs<T, W>(m, face, x, y);
 }
 
-// A brick's slots; those of any slab layout are at most as many (use_wide_slabs,
+// A brick's slots; those of any slab layout are at most as many (wide_slabs,
 // Slab::NFACE).  This is the bound that mf.h states for mf_operator_apply_noalloc.
 int64_t face_buffer_elems(const KMesh &m) { return n_bricks(m) * BFACE; }
 
@@ -573,9 +573,57 @@ static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void
 // 18.4 / 18.0.
 static bool use_tiles(const KMesh &m, const HeatArgs &a) { return Tile::count(m) <= (a.mode == 2 ? 1024 : 2048); }
 
-static bool wide_slabs(const KMesh &m, const HeatArgs &a)
+// Slabs of four sub-bricks or of one (FP64; FP32: slab_width_fp32).  The SIMDs
+// take two wavefronts of these kernels each, so a launch runs in half rounds of
+// 1024 bricks, or of 256 slabs.  Slabs of four shorten the combine pass and use
+// whole lines, but pay for every empty slot along x and for a partly filled last
+// round.  From `lo` bricks on they are taken where they need no more half rounds
+// than single bricks; from `big` on, where the fields outgrow the caches and the
+// lines decide, where enough of their slots hold cells (`filled`).  The forms with more work per cell (a third staged field,
+// the sine Heaviside, whose polynomial only some wavefronts of a slab evaluate)
+// gain least from the combine.  Below three slots of four a slab's slots exceed
+// the face buffer.  Four / one sub-brick, us per apply (half rounds, filled slots):
+//   linear      44^3 (2 / 2, 11 of 12) 17.7 / 18.2, 42x58x47 (3 / 2, 11 of 12) 22.2 / 19.4,
+//               53x70x61 (5 / 4, 14 of 16) 32.6 / 30.2, 64^3 (4 / 4) 30.5 / 32.3, 70^3
+//               (7 / 6) 40.6 / 39.5, 80^3 (8 / 8) 47.3 / 51.3, 104^3 (19 / 18) 105 / 127
+//   per point   57^3 35.2 / 32.4 (15 of 16), 70^3 51.4 / 50.2, 76^3 69.7 / 78.1, 36x200x200
+//               (9 of 12) 266 / 276
+//   sine        57^3 34.1 / 32.0, 64^3 36.1 / 35.7, 88^3 74.2 / 70.3, 96^3 86.8 / 95.1,
+//               36x200x200 178 / 163, 68x160x160 (17 of 20) 199 / 200
+//   convective  57^3 41.9 / 39.6, 70^3 64.1 / 57.5, 80^3 74.8 / 76.6, 82x87x71 (21 of 24)
+//               86.1 / 76.6 (10 / 9), 84^3 100 / 104, 96^3 139 / 164, 36x200x200 272 / 269;
+//               with the sine form 88^3 127 / 129, 91x98x86 (23 of 24) 145 / 151
+//   three phases 57^3 40.7 / 40.4, 70^3 (7 / 6) 60.1 / 56.5, 79x69x75 (7 / 7) 62.0 / 64.2, 80^3
+//               69.5 / 73.4, 36x200x200 238 / 212, 68x160x160 259 / 261; with the sine form
+//               88^3 126 / 118, 96^3 150 / 156, 100^3 (25 of 28) 182 / 176
+// In a CG iteration the vector kernels between the applies are the same, and the
+// lines lie a little elsewhere (40 iterations on 45x64x51 linear 1.82 / 1.85 ms,
+// 61x53x64 2.28 / 2.32, 80^3 4.16 / 4.29; per point 62^3 2.73 / 2.74, 72^3 4.57 / 4.67).
+static bool wide_slabs(const KMesh &m, const HeatArgs &a, bool cg)
 {
-    return use_wide_slabs(m, a.conv != 0 || a.mode != 0 || a.hkind != 0);
+    const int64_t nb = n_bricks(m), none = INT64_MAX;
+    const int used = (int)ceil_div(m.nx, BB), slots = 4 * (int)ceil_div(m.nx, 4 * BB);
+    if (4 * used < 3 * slots) return false;
+    const bool sine = a.mode != 1 && a.hkind;
+    int64_t lo = none, big = 13000;
+    bool filled = true;
+    if (a.mode == 1) {
+        lo = cg ? 4000 : none;
+        big = cg ? 5000 : 6400;
+    } else if (a.mode == 2) {
+        lo = sine ? none : 6000;
+        filled = sine ? 16 * used > 15 * slots : 6 * used > 5 * slots;
+    } else if (a.conv) {
+        lo = sine ? none : 8000;
+        big = sine ? 12000 : 9000;
+        filled = 6 * used > 5 * slots;
+    } else if (sine) {
+        filled = 6 * used > 5 * slots;
+    } else {
+        lo = cg ? 3300 : 1200;
+    }
+    if (nb >= big && filled) return true;
+    return nb >= lo && (n_slabs<4>(m) + 255) / 256 <= (nb + 1023) / 1024;
 }
 
 // Sub-bricks per slab of the FP32 applies.  A brick's FP32 rows of 36 bytes use
@@ -619,7 +667,7 @@ static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const voi
         const int w = slab_width_fp32(m, a);
         if (w == 4) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
         if (w == 2) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 2>(m, a, x, y, face, cg, r, s, ev0, ev1);
-    } else if (wide_slabs(m, a)) {
+    } else if (wide_slabs(m, a, CGF)) {
         return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
     }
     return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 1>(m, a, x, y, face, cg, r, s, ev0, ev1);
