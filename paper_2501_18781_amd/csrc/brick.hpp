@@ -69,7 +69,8 @@ __host__ __device__ __forceinline__ constexpr int face_slot(int lx, int ly, int 
 
 struct Brick {
     static constexpr int NT = BNT, PZ = BP, NNODES = BNB, NFACE = BFACE;
-    static constexpr int CX = BB; // cells along x
+    static constexpr int W = 1, CX = BB; // wavefronts; cells along x
+    template <typename T> static __host__ __device__ constexpr int field() { return lds_field<T>(); }
     static __device__ __forceinline__ constexpr int face_slot_of(int lx, int ly, int lz) { return face_slot(lx, ly, lz); }
 
     int brick;         // natural brick index (x fastest)
@@ -143,6 +144,12 @@ struct Brick {
                ((f & 8u) && c0y + ncy == m.ny) || ((f & 16u) && c0z == 0) || ((f & 32u) && c0z + ncz == m.nz);
     }
 
+    // Neighbours on all six sides (and so no Dirichlet face).
+    __device__ __forceinline__ bool inner(const KMesh &m) const
+    {
+        return bx > 0 && by > 0 && bz > 0 && c0x + BB < m.nx && c0y + BB < m.ny && c0z + BB < m.nz;
+    }
+
     // Visit the nodes this thread owns: f(a, b, c, lds_index, global_index,
     // constrained, shared), with a, b, c compile-time constants and
     // lds_index in the layout of a staged field of T.  `shared` is
@@ -185,16 +192,13 @@ struct Brick {
         // brick's low faces and every high node is shared.  Such bricks take
         // a copy of the visits with these flags folded in (a uniform branch;
         // 26.1 -> 25.6 us for the FP64 apply kernel at 64^3).
-        const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB, nbz = (m.nz + BB - 1) / BB;
-        const bool inner = bx > 0 && by > 0 && bz > 0 && bx < nbx - 1 && by < nby - 1 && bz < nbz - 1 &&
-                           !touches_dirichlet(m);
         auto inode = [&](auto A, auto B, auto C) {
             constexpr int a = decltype(A)::value, b = decltype(B)::value, c = decltype(C)::value;
             constexpr bool hi = a == 2 || b == 2 || c == 2;
             const bool shared = hi || (a == 0 && tx == 0) || (b == 0 && ty == 0) || (c == 0 && tz == 0);
             f(a, b, c, l0 + a + R * b + P * c, g0 + a + sy * b + sz * c, false, (shared ? 1 : 0) | (hi ? 2 : 0));
         };
-        if (inner) {
+        if (inner(m)) {
             inode(I0{}, I0{}, I0{}); inode(I1{}, I0{}, I0{}); inode(I0{}, I1{}, I0{}); inode(I1{}, I1{}, I0{});
             inode(I0{}, I0{}, I1{}); inode(I1{}, I0{}, I1{}); inode(I0{}, I1{}, I1{}); inode(I1{}, I1{}, I1{});
             if (lastx) { inode(I2{}, I0{}, I0{}); inode(I2{}, I1{}, I0{}); inode(I2{}, I0{}, I1{}); inode(I2{}, I1{}, I1{}); }
@@ -371,6 +375,13 @@ struct Brick {
             T *const dst[2] = {l0s, l1s};
             stage_rows<NT, 2, false, T>(m, t, src, dst, 0u);
         }
+    }
+
+    // NF FP64 fields by the brick's lanes (the slabs' interface).
+    template <int NF>
+    __device__ __forceinline__ void stage(const KMesh &m, const double *const (&src)[NF], double *const (&dst)[NF]) const
+    {
+        stage_rows<NT, NF, false, double>(m, t, src, dst, 0u);
     }
 
     // NF FP64 fields over a workgroup of WG threads; bit f of maskbits: field f
@@ -609,10 +620,8 @@ __device__ __forceinline__ void combine_brick_visit(const KMesh &m, int brick, i
 {
     const Brick br(m, lane, brick);
     const int nbx = (m.nx + BB - 1) / BB, nby = (m.ny + BB - 1) / BB, nbz = (m.nz + BB - 1) / BB;
-    const bool inner = br.bx > 0 && br.by > 0 && br.bz > 0 && br.bx < nbx - 1 && br.by < nby - 1 &&
-                       br.bz < nbz - 1 && !br.touches_dirichlet(m);
     constexpr int L = BNT; // a wavefront per brick
-    if (inner) combine_brick_nodes<T, SKIP_CONSTRAINED, L, true>(m, br, nbx, nby, nbz, lane, face, f);
+    if (br.inner(m)) combine_brick_nodes<T, SKIP_CONSTRAINED, L, true>(m, br, nbx, nby, nbz, lane, face, f);
     else combine_brick_nodes<T, SKIP_CONSTRAINED, L, false>(m, br, nbx, nby, nbz, lane, face, f);
 }
 
@@ -1115,19 +1124,19 @@ __device__ __forceinline__ void finish_tile(const KMesh &m, const Tile &br, T *_
     });
 }
 
-// Lanes that finish one slab's shared nodes, at most five nodes each.
-template <int W> __host__ __device__ constexpr int combine_lanes() { return W == 1 ? BNT : 2 * BNT; }
+// Lanes that finish one slab's (or brick's) shared nodes, at most five nodes each.
+template <typename SL> __host__ __device__ constexpr int combine_lanes() { return SL::W == 1 ? BNT : 2 * BNT; }
 constexpr int SCT = 256; // threads of a slab-combine workgroup
 
-// The combine pass of an apply on slabs: y = x on Dirichlet nodes.
-template <typename T, int W>
+// The combine pass of an apply on slabs or bricks: y = x on Dirichlet nodes.
+template <typename T, typename SL>
 __device__ __forceinline__ void combine_slabs(const KMesh &m, const T *__restrict__ face, const T *__restrict__ x,
                                               T *__restrict__ y)
 {
-    constexpr int L = combine_lanes<W>(), PER = SCT / L;
+    constexpr int L = combine_lanes<SL>(), PER = SCT / L;
     const int slab = Brick::xcd_index() * PER + (int)threadIdx.x / L, lane = (int)threadIdx.x % L;
-    if (slab >= n_slabs<W>(m)) return; // whole wavefronts; no barrier follows in them
-    const Slab<W> br(m, lane, slab);
+    if (slab >= n_slabs<SL::W>(m)) return; // whole wavefronts; no barrier follows in them
+    const SL br(m, lane, slab);
     const int nbx = (int)ceil_div(m.nx, br.CX), nby = (int)ceil_div(m.ny, BB), nbz = (int)ceil_div(m.nz, BB);
     auto f = [&](int64_t g, bool constrained, T s) { y[g] = constrained ? x[g] : s; };
     if (br.inner(m)) combine_brick_nodes<T, true, L, true>(m, br, nbx, nby, nbz, lane, face, f);

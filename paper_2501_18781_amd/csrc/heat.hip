@@ -323,28 +323,31 @@ __device__ __forceinline__ void heat_conv_cell_apply(const BR &br, const KMesh &
 }
 
 // CONV: 0 plain heat operator; 1 with the convective term; 2 its transpose
-// (FP64, level-set coefficients, no CG epilogue).  W sub-bricks per workgroup
-// (brick.hpp: Slab).  The cell work and the node sums of a sub-brick are the
+// (FP64, level-set coefficients, no CG epilogue).  SL: the workgroup's unit of
+// work, a slab of W sub-bricks, an overlapping tile or a brick (brick.hpp).
+// Slabs: the cell work and the node sums of a sub-brick are the
 // wavefront's own; the nodes are staged, summed across the sub-bricks and
 // finished by the whole workgroup, row by row.  LDS: x (stays for the
 // Dirichlet rows and the CG epilogue); phi, then the node sums; and with
 // W > 1 a third region for the z exchange of the node sums (with W = 1 that
 // overlays phi), which holds the frozen temperature or one velocity
-// component before.
-// TILE: an overlapping tile (brick.hpp) in place of a slab of one brick.
+// component before.  Bricks: the node sums stay in registers and each cell
+// finishes the nodes that it owns.
 // CG: the epilogue sums p.Ap.  DIR (with CG): x is p = z + beta p_old, formed in
 // the staging from the previous iteration's residual partials (CGDir); once
 // converged only x is completed.
-template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W, bool DIR, bool TILE>
-__device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &a, const T *__restrict__ x,
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, typename SL, bool DIR>
+__device__ __forceinline__ void heat_apply_unit(const KMesh &m, const HeatArgs &a, const T *__restrict__ x,
                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
                                                 double *partials, const CGDir &dir)
 {
-    static_assert(!DIR || (CG && W == 1 && std::is_same<T, double>::value), "the direction update is CG's");
+    constexpr bool TILE = std::is_same<SL, Tile>::value, BRICK = std::is_same<SL, Brick>::value;
+    constexpr int W = SL::W;
+    static_assert(!DIR || (CG && std::is_same<SL, Slab<1>>::value && std::is_same<T, double>::value),
+                  "the direction update is CG's");
     static_assert(CONV == 0 || (std::is_same<T, double>::value && MODE == 0 && !CG), "convective form: FP64 only");
     static_assert(MODE != 2 || std::is_same<T, double>::value, "three-phase coefficients: FP64 only");
-    static_assert(!TILE || (!CG && W == 1), "a tile computes nodes that it does not own");
-    using SL = std::conditional_t<TILE, Tile, Slab<W>>;
+    static_assert(!TILE || !CG, "a tile computes nodes that it does not own");
     constexpr int NF = SL::template field<T>(), XCH = W > 1 ? 9 * SL::NT : 0;
     static_assert(NF >= 9 * BNT, "with W = 1 the z exchange overlays phi");
     constexpr int THIRD = (MODE == 2 || CONV != 0) && NF > XCH ? NF : XCH;
@@ -440,20 +443,33 @@ __device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &
         else heat_cell_apply<T>(u, cm, ck, ihx, ihy, ihz);
     }
     __syncthreads(); // phi and the third region no longer read
-    br.assemble(u, W > 1 ? ts + 9 * BNT * br.w : ps, ps, xhi);
-    __syncthreads();
-
     double energy = 0.0;
-    T v[SL::NV], xv[SL::NV];
-    br.node_values(m, ps, xhi, v);
-    if (CG || br.dirichlet_faces(m)) {
-        br.read_nodes(m, xs, xv);
+    if constexpr (BRICK) {
+        br.assemble27(u, ps);
+        // x.Ax: x_i times the brick's partial sum at node i, with x_i^2 for a
+        // Dirichlet node counted once, by the brick that finishes it
+        T *fb = face + (int64_t)br.brick * Brick::NFACE;
+        br.template for_owned_nodes<T>(m, [&](int ai, int bi, int ci, int l, int64_t g, bool constrained, int sh) {
+            const T xv = xs[l], s = u[ai + 3 * bi + 9 * ci];
+            if (CG) energy += constrained ? ((sh & 2) ? 0.0 : (double)xv * (double)xv) : (double)xv * (double)s;
+            T *dst = sh ? fb + br.fslot(ai, bi, ci) : y + g;
+            *dst = constrained ? xv : s;
+        });
     } else {
+        br.assemble(u, W > 1 ? ts + 9 * BNT * br.w : ps, ps, xhi);
+        __syncthreads();
+
+        T v[SL::NV], xv[SL::NV];
+        br.node_values(m, ps, xhi, v);
+        if (CG || br.dirichlet_faces(m)) {
+            br.read_nodes(m, xs, xv);
+        } else {
 #pragma unroll
-        for (int k = 0; k < SL::NV; ++k) xv[k] = T(0);
+            for (int k = 0; k < SL::NV; ++k) xv[k] = T(0);
+        }
+        if constexpr (TILE) finish_tile<T>(m, br, y, v, xv);
+        else finish_nodes<T, CG>(m, br, y, face, v, xv, energy);
     }
-    if constexpr (TILE) finish_tile<T>(m, br, y, v, xv);
-    else finish_nodes<T, CG>(m, br, y, face, v, xv, energy);
     if (CG) {
         // one partial per slab; the alpha kernel sums them in slab order
         double tot = wave_total(energy);
@@ -468,25 +484,25 @@ __device__ __forceinline__ void heat_apply_slab(const KMesh &m, const HeatArgs &
     }
 }
 
-template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W>
-__global__ void __launch_bounds__(Slab<W>::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
-                                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
-                                                                 RedWS red)
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, typename SL>
+__global__ void __launch_bounds__(SL::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
+                                                            T *__restrict__ y, T *__restrict__ face, CGState *cg,
+                                                            RedWS red)
 {
-    heat_apply_slab<T, MODE, HK, CG, CONV, ISO, W, false, false>(m, a, x, y, face, cg, red.partials, CGDir{});
+    heat_apply_unit<T, MODE, HK, CG, CONV, ISO, SL, false>(m, a, x, y, face, cg, red.partials, CGDir{});
 }
 
 template <typename T, int MODE, int HK, int CONV, bool ISO>
 __global__ void __launch_bounds__(BNT) heat_tile_kernel(KMesh m, HeatArgs a, const T *__restrict__ x, T *__restrict__ y)
 {
-    heat_apply_slab<T, MODE, HK, false, CONV, ISO, 1, false, true>(m, a, x, y, nullptr, nullptr, nullptr, CGDir{});
+    heat_apply_unit<T, MODE, HK, false, CONV, ISO, Tile, false>(m, a, x, y, nullptr, nullptr, nullptr, CGDir{});
 }
 
 template <int MODE, int HK, bool ISO>
 __global__ void __launch_bounds__(BNT) heat_cg_apply_kernel(KMesh m, HeatArgs a, CGDir dir, double *__restrict__ q,
                                                             double *__restrict__ face, CGState *cg, double *ppart)
 {
-    heat_apply_slab<double, MODE, HK, true, 0, ISO, 1, true, false>(m, a, nullptr, q, face, cg, ppart, dir);
+    heat_apply_unit<double, MODE, HK, true, 0, ISO, Slab<1>, true>(m, a, nullptr, q, face, cg, ppart, dir);
 }
 
 // alpha = rz / p.Ap from the partials of a CG-mode apply, by one workgroup.
@@ -522,8 +538,8 @@ __global__ void __launch_bounds__(BNT * CBW) face_combine_brick_kernel(KMesh m, 
     combine_brick<T, DMODE>(m, face, nullptr, y);
 }
 
-// The same for an apply: slabs, y = x on Dirichlet nodes, and alpha with CG.
-template <typename T, bool CG, int W>
+// The same for an apply: slabs or bricks, y = x on Dirichlet nodes, and alpha with CG.
+template <typename T, bool CG, typename SL>
 __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__restrict__ face, const T *__restrict__ x,
                                                            T *__restrict__ y, CGState *cg,
                                                            const double *__restrict__ partials, unsigned nslabs)
@@ -532,7 +548,7 @@ __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__r
         if (cg->done) return;
         if (blockIdx.x == 0) cg_set_alpha<SCT>(cg, partials, nslabs);
     }
-    combine_slabs<T, W>(m, face, x, y);
+    combine_slabs<T, SL>(m, face, x, y);
 }
 
 // A brick's slots; those of any slab layout are at most as many (wide_slabs,
@@ -543,23 +559,23 @@ int64_t face_buffer_elems(const KMesh &m) { return n_bricks(m) * BFACE; }
 // (with CG, alpha from the slabs' partials of p.Ap).  With timing on, the
 // events are attached to the slab kernel's own dispatch (they record its
 // start and end, not the neighbouring queue packets).
-template <typename T, int MODE, int HK, bool CGF, int CV, bool ISO, int W>
+template <typename SL, typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
 static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face, CGState *cg,
                                    const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
-    const unsigned ns = (unsigned)n_slabs<W>(m);
-    constexpr int NT = Slab<W>::NT;
+    const unsigned ns = (unsigned)n_slabs<SL::W>(m);
+    constexpr int NT = SL::NT;
     if (ev0)
-        hipExtLaunchKernelGGL(heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, W>, dim3(ns), dim3(NT), 0, s, ev0, ev1, 0, m,
+        hipExtLaunchKernelGGL(heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, SL>, dim3(ns), dim3(NT), 0, s, ev0, ev1, 0, m,
                               a, (const T *)x, (T *)y, (T *)face, cg, r);
     else
-        heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, W><<<ns, NT, 0, s>>>(m, a, (const T *)x, (T *)y, (T *)face, cg, r);
+        heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, SL><<<ns, NT, 0, s>>>(m, a, (const T *)x, (T *)y, (T *)face, cg, r);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // a single slab shares nothing; alpha from its partial
     if (ns == 1) return CGF ? cg_alpha(cg, &r, ns, s) : hipSuccess;
-    constexpr unsigned PER = SCT / combine_lanes<W>();
-    slab_combine_kernel<T, CGF, W><<<(ns + PER - 1) / PER, SCT, 0, s>>>(
+    constexpr unsigned PER = SCT / combine_lanes<SL>();
+    slab_combine_kernel<T, CGF, SL><<<(ns + PER - 1) / PER, SCT, 0, s>>>(
         m, (const T *)face, (const T *)x, (T *)y, CGF ? cg : nullptr, CGF ? r.partials : nullptr, CGF ? ns : 0u);
     return hipGetLastError();
 }
@@ -596,9 +612,11 @@ static bool use_tiles(const KMesh &m, const HeatArgs &a) { return Tile::count(m)
 //   three phases 57^3 40.7 / 40.4, 70^3 (7 / 6) 60.1 / 56.5, 79x69x75 (7 / 7) 62.0 / 64.2, 80^3
 //               69.5 / 73.4, 36x200x200 238 / 212, 68x160x160 259 / 261; with the sine form
 //               88^3 126 / 118, 96^3 150 / 156, 100^3 (25 of 28) 182 / 176
-// In a CG iteration the vector kernels between the applies are the same, and the
-// lines lie a little elsewhere (40 iterations on 45x64x51 linear 1.82 / 1.85 ms,
-// 61x53x64 2.28 / 2.32, 80^3 4.16 / 4.29; per point 62^3 2.73 / 2.74, 72^3 4.57 / 4.67).
+// In a CG iteration, whose vectors share the caches and whose single bricks are
+// conv_bricks' (below), the lines lie a little elsewhere.  Slabs of four / bricks,
+// 40 iterations: linear 50x37x61 (3 / 3) 1.77 / 1.70 ms, 61x53x64 (4 / 4) 2.28 / 2.28, 80^3
+// 4.16 / 4.28, 84^3 (11 / 10) 5.14 / 5.48; sine 80^3 4.58 / 4.53, 84^3 5.55 / 5.75; per point
+// 62^3 2.73 / 2.77, 72^3 4.57 / 4.82.
 static bool wide_slabs(const KMesh &m, const HeatArgs &a, bool cg)
 {
     const int64_t nb = n_bricks(m), none = INT64_MAX;
@@ -617,13 +635,31 @@ static bool wide_slabs(const KMesh &m, const HeatArgs &a, bool cg)
         lo = sine ? none : 8000;
         big = sine ? 12000 : 9000;
         filled = 6 * used > 5 * slots;
-    } else if (sine) {
-        filled = 6 * used > 5 * slots;
     } else {
-        lo = cg ? 3300 : 1200;
+        if (cg) big = 9000;
+        if (sine) filled = 6 * used > 5 * slots;
+        else lo = cg ? 3300 : 1200;
     }
     if (nb >= big && filled) return true;
     return nb >= lo && (n_slabs<4>(m) + 255) / 256 <= (nb + 1023) / 1024;
+}
+
+// Bricks in place of slabs of one brick, FP64: no row-wise finishing through LDS,
+// which pays where a wavefront's latency counts and costs where the other
+// wavefront of the SIMD hides that and the LDS is busy.  Slab of one / brick, us:
+//   three phases 38^3 18.9 / 18.3, 42^3 24.7 / 24.1, 56^3 35.4 / 34.9, 62^3 43.0 / 42.3 (with the
+//               sine form the slab: 56^3 48.3 / 49.4, 45^3 34.9 / 35.1)
+//   convective  44^3 24.8 / 25.0, 40x50x47 (1560 bricks) 25.4 / 25.4, 48^3 27.4 / 26.8, 80x80x20
+//               29.3 / 27.9, 56^3 35.5 / 34.8, 62^3 43.0 / 42.9, 66x73x63 (5168) 53.5 / 54.8, 75x69x73
+//               62.7 / 64.5; transposed 56^3 34.2 / 35.2; from 9000 bricks on, beyond the
+//               caches, where it wastes slots to be a slab of four: 36x200x200 269 / 260,
+//               transposed 265 / 256
+//   CG, four launches, 40 iterations: linear 42x52x41 1.53 / 1.48 ms, 56^3 2.04 / 1.99; sine 48^3
+//               1.74 / 1.79, 56^3 2.14 / 2.15; per point 53^3 2.06 / 2.05; three phases 56^3 2.44 / 2.39
+static bool conv_bricks(const KMesh &m, int conv) // (three phases and CG: always)
+{
+    const int64_t nb = n_bricks(m);
+    return nb >= 9000 || (conv == 1 && nb >= 1536 && nb < 5000);
 }
 
 // Sub-bricks per slab of the FP32 applies.  A brick's FP32 rows of 36 bytes use
@@ -663,14 +699,24 @@ static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const voi
             return hipGetLastError();
         }
     }
+#define UNIT_LAUNCH(SL) heat_slab_launch<SL, T, MODE, HK, CGF, CV, ISO>(m, a, x, y, face, cg, r, s, ev0, ev1)
     if constexpr (sizeof(T) == 4) {
         const int w = slab_width_fp32(m, a);
-        if (w == 4) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
-        if (w == 2) return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 2>(m, a, x, y, face, cg, r, s, ev0, ev1);
-    } else if (wide_slabs(m, a, CGF)) {
-        return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 4>(m, a, x, y, face, cg, r, s, ev0, ev1);
+        if (w == 4) return UNIT_LAUNCH(Slab<4>);
+        if (w == 2) return UNIT_LAUNCH(Slab<2>);
+        return UNIT_LAUNCH(Slab<1>);
+    } else {
+        if (wide_slabs(m, a, CGF)) return UNIT_LAUNCH(Slab<4>);
+        if constexpr (CGF || (MODE == 2 && HK == 0)) {
+            return UNIT_LAUNCH(Brick);
+        } else {
+            if constexpr (CV != 0) {
+                if (conv_bricks(m, CV)) return UNIT_LAUNCH(Brick);
+            }
+            return UNIT_LAUNCH(Slab<1>);
+        }
     }
-    return heat_slab_launch<T, MODE, HK, CGF, CV, ISO, 1>(m, a, x, y, face, cg, r, s, ev0, ev1);
+#undef UNIT_LAUNCH
 }
 
 hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x, void *y, void *face, CGState *cg,

@@ -98,18 +98,20 @@ def test_fp32(gpu, n, form, equal):
     check(n, form, mf.MF_FP32, equal)
 
 
-# FP64.  Slabs of one; slabs of four in which a sub-brick or more is empty: 11 of
+# FP64.  Bricks: three phases, the convective form and, beyond 9000 bricks, its
+# transpose; slabs of one; slabs of four in which a sub-brick or more is empty: 11 of
 # 12 slots (1320 bricks), 9 of 12 (13338), 22 of 24 (13200), 18 of 20 (6840), 21
 # of 24 (10164), 19 of 20 (7220), 23 of 24 (13248)
+BRICK = [((38, 41, 35), "melt", False), ((45, 50, 51), "conv", True), ((45, 50, 51), "conv sine", False),
+         ((35, 129, 131), "conv", False)]
 ONE = [((42, 58, 47), "linear", False), ((50, 37, 61), "sine", False), ((41, 42, 43), "points", True),
-       ((45, 41, 39), "conv", True), ((45, 41, 39), "conv sine", False), ((38, 41, 35), "melt", False),
-       ((38, 41, 35), "melt sine", True)]
+       ((45, 41, 39), "conv", True), ((45, 41, 39), "conv sine", False), ((38, 41, 35), "melt sine", True)]
 FOUR = [((43, 47, 39), "linear", True), ((35, 151, 153), "linear", False), ((86, 98, 95), "sine", True),
         ((69, 75, 78), "points", False), ((83, 86, 87), "conv", False), ((86, 98, 95), "conv sine", True),
         ((73, 76, 79), "melt", True), ((91, 95, 96), "melt sine", False)]
 
 
-@pytest.mark.parametrize("n,form,equal", ONE + FOUR)
+@pytest.mark.parametrize("n,form,equal", BRICK + ONE + FOUR)
 def test_fp64(gpu, n, form, equal):
     assert tiles(n) > 2048
     check(n, form, mf.MF_FP64, equal)
