@@ -237,7 +237,6 @@ HeatArgs heat_args(const mf_operator *op)
     HeatArgs a;
     a.mode = op->coeff_mode == MF_COEFF_QUAD ? 1 : 0;
     a.hkind = op->heaviside;
-    a.eps = op->eps;
     a.am = op->alpha_m;
     a.ak = op->alpha_k;
     a.k_l = op->k_l;
@@ -264,7 +263,6 @@ OseenArgs oseen_args(const mf_operator *op)
 {
     OseenArgs a;
     a.hkind = op->heaviside;
-    a.eps = op->eps;
     a.am = op->alpha_m;
     a.ac = op->alpha_c;
     a.av = op->alpha_v;

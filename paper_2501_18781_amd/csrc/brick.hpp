@@ -4,10 +4,10 @@
 // thread per cell; the brick's 9x9x9 Q2 nodes are staged in LDS.  The heat
 // applies use the same cells and node sums in slabs (Slab, below).
 //
-// Staging is per cell (each thread reads the 27 nodes of its cell and
+// Staging of a brick is per node (the lanes stage its 9-node rows; FP64) or, in
+// the FP32 diagonal, per cell (each thread reads the 27 nodes of its cell and
 // writes them to LDS; nodes shared by cells of the brick are written with
-// the same value by each) or per node (the lanes stage whole 9-node rows of
-// the brick; used by the FP64 kernels).  Finishing is by ownership: a cell owns its
+// the same value by each).  Finishing is by ownership: a cell owns its
 // local nodes (a, b, c) with a, b, c in {0, 1}, and the last valid cell of
 // the brick in a direction also owns the local nodes with index 2 in that
 // direction, so every brick node is finished by exactly one thread, with
@@ -464,8 +464,7 @@ struct Brick {
     // and in y lane t - 4, both in the same 16-lane row (a DPP row shift;
     // the first cell of an x line is masked, the first of a y line is at a
     // row's start and takes zero), and in z lane t - 16, exchanged through
-    // LDS (xch, 9 NT values; with two wavefronts per brick the exchange
-    // between tz = 3 and tz = 4 crosses them).  The sums run x, then y, then z: a fixed order.
+    // LDS (xch, 9 NT values).  The sums run x, then y, then z: a fixed order.
     // All lanes of the wavefront must call it.
     template <typename T> __device__ __forceinline__ void assemble27(T *u, T *xch) const
     {
@@ -526,7 +525,7 @@ struct Brick {
 // ---------------------------------------------------------------------------
 
 // Brick-owned combine: a wavefront per brick (numbered like the brick
-// kernels, XCD-contiguously), two per slab of four sub-bricks.  Each shared node is finished
+// kernels, XCD-contiguously), two per slab of two or four sub-bricks.  Each shared node is finished
 // by the one brick that holds it at local index 0 in every direction in
 // which it is shared: the brick's nodes on its low faces that lie on
 // internal brick planes, without its shared high faces (the next brick's
@@ -540,7 +539,7 @@ struct Brick {
 // that enumerates the shared nodes flat, which this pass replaced with
 // bitwise the same results); all loads of a lane's nodes are issued before
 // the sums.
-// The visit for one brick (or slab: BR gives the extents, CX x BB x CZ cells,
+// The visit for one brick (or slab: BR gives the extents, CX x BB x BB cells,
 // and the face-buffer slots); INNER: a brick with neighbours on all six sides
 // and no Dirichlet face, for which the ranges, the sharing flags and the
 // divisions are compile-time constants and nothing is constrained.  L lanes

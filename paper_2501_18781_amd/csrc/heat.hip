@@ -9,8 +9,8 @@
 // (FP64, level-set coefficients); its transpose moves the derivative onto
 // the test function: alpha_c rc_q x_q u_q . grad N_i.
 //
-// Work decomposition of the applies (brick.hpp): workgroups of one or four
-// wavefronts, each a brick of 4x4x4 cells, one thread per cell.
+// Work decomposition of the applies (brick.hpp): workgroups of one, two (FP32) or
+// four wavefronts, each a brick of 4x4x4 cells, one thread per cell.
 //   1. the workgroup's nodal x and phi are staged in LDS row by row, each
 //      node read once; Dirichlet columns read as zero when x is gathered;
 //   2. each thread evaluates its cell entirely in registers by sum
@@ -20,8 +20,8 @@
 //   3. each owned node sums the (at most 8) cells of the brick that share it
 //      in a fixed order, in registers (cross-lane shifts in x and y, an LDS
 //      exchange in z);
-//   4. the node sums pass through LDS; nodes complete within the workgroup
-//      are stored; nodes on a face shared with a neighbour go to a face
+//   4. the node sums pass through LDS (bricks: stay in registers); nodes
+//      complete within the workgroup are stored; nodes on a face shared with a neighbour go to a face
 //      buffer, and a second kernel adds the partials sharing each such node
 //      in a fixed order, brick by brick.  Every output entry is written once, without
 //      atomics, and the result is bitwise reproducible.  Dirichlet nodes get
@@ -523,14 +523,9 @@ __device__ __forceinline__ void cg_set_alpha(CGState *cg, const double *__restri
     }
 }
 
-// Second pass of an apply, a diagonal or a gradient: the shared nodes, each
-// the sum of the bricks' face partials in a fixed order, finished brick by
-// brick (combine_brick in brick.hpp).  In CG mode the first workgroup first
-// sums the bricks' partials of p.Ap (complete once the brick kernel has
-// finished) and sets alpha = rz / p.Ap, which saves a launch per
-// iteration.  A breakdown sets done here; a workgroup of this launch that
-// then skips its nodes leaves q incomplete, which no later step of the
-// solve reads.
+// Second pass of a diagonal or a gradient: the shared nodes, each the sum of the
+// bricks' face partials in a fixed order, finished brick by brick (combine_brick
+// in brick.hpp).
 template <typename T, int DMODE>
 __global__ void __launch_bounds__(BNT * CBW) face_combine_brick_kernel(KMesh m, const T *__restrict__ face,
                                                                        T *__restrict__ y)
@@ -538,7 +533,11 @@ __global__ void __launch_bounds__(BNT * CBW) face_combine_brick_kernel(KMesh m, 
     combine_brick<T, DMODE>(m, face, nullptr, y);
 }
 
-// The same for an apply: slabs or bricks, y = x on Dirichlet nodes, and alpha with CG.
+// The same for an apply: slabs or bricks, y = x on Dirichlet nodes.  In CG mode
+// the first workgroup first sums the slabs' partials of p.Ap (complete once the
+// slab kernel has finished) and sets alpha = rz / p.Ap, which saves a launch per
+// iteration.  A breakdown sets done here; a workgroup of this launch that then
+// skips its nodes leaves q incomplete, which no later step of the solve reads.
 template <typename T, bool CG, typename SL>
 __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__restrict__ face, const T *__restrict__ x,
                                                            T *__restrict__ y, CGState *cg,

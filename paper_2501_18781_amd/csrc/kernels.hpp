@@ -13,7 +13,6 @@ namespace mf {
 struct HeatArgs {
     int mode;        // 0: from nodal phi, 1: per quadrature point
     int hkind;       // Heaviside form
-    double eps;
     double am, ak;   // alpha_m, alpha_k
     double k_l, k_g, rc_l, rc_g;
     const void *phi, *kq, *rcq;
@@ -49,7 +48,6 @@ struct TransportArgs {
 // Coefficients of the Oseen operator.
 struct OseenArgs {
     int hkind;
-    double eps;
     double am, ac, av;
     double rho_l, rho_g, mu_l, mu_g;
     const double *phi, *u0;
@@ -84,11 +82,11 @@ struct KTiming {
 };
 
 // ---- heat (heat.hip) ----
-// y = A x in two launches (slabs, then the shared-face combine), on small
-// meshes in one (overlapping tiles, without CG); `face` is
-// a workspace of face_buffer_elems(m) elements of the operator's type.  With
-// cg != nullptr (FP64 only) the apply also forms p.Ap from per-brick
-// partials and a third, single-workgroup launch sets alpha = rz / p.Ap.
+// y = A x in two launches (slabs or bricks, then the shared-face combine), on
+// small meshes in one (overlapping tiles, without CG); `face` is a workspace of
+// face_buffer_elems(m) elements of the operator's type.  With cg != nullptr (FP64
+// only) the apply also forms p.Ap from per-slab partials, and the first workgroup
+// of the combine (with a single slab: a launch of its own) sets alpha = rz / p.Ap.
 hipError_t heat_apply(const KMesh &m, const HeatArgs &a, int fp32, const void *x, void *y, void *face, CGState *cg,
                       const RedWS *red, hipStream_t s, const KTiming *t = nullptr);
 int64_t face_buffer_elems(const KMesh &m);

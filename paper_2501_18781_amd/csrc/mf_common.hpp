@@ -183,22 +183,6 @@ template <typename T> __device__ __forceinline__ void interp3T(T *v)
     line_apply<T, 2>(v, v, f);
 }
 
-template <typename T, int DIR> __device__ __forceinline__ void deriv_dir(const T *in, T *out)
-{
-    auto f = [](T a, T b, T c, T &x, T &y, T &z) { Q2<T>::deriv(a, b, c, x, y, z); };
-    line_apply<T, DIR>(in, out, f);
-}
-
-template <typename T, int DIR> __device__ __forceinline__ void derivT_acc_dir(const T *in, T *acc)
-{
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-        for (int m = 0; m < 3; ++m)
-            Q2<T>::derivT_acc(in[lidx<DIR>(0, m, n)], in[lidx<DIR>(1, m, n)], in[lidx<DIR>(2, m, n)],
-                              acc[lidx<DIR>(0, m, n)], acc[lidx<DIR>(1, m, n)], acc[lidx<DIR>(2, m, n)]);
-}
-
 // Along direction DIR, line by line: t = ih D' u, g = c .* t, acc += D'^T g.
 // Working on one 3-point line at a time keeps only 3 temporaries live.
 template <typename T, int DIR, typename C>
@@ -252,26 +236,6 @@ __device__ __forceinline__ void pin27(double *v)
     for (int i = 0; i < 27; ++i) asm volatile("" : "+v"(v[i])::"memory");
 }
 
-// Convection along DIR, line by line, with t = D'_DIR u the collocation derivative:
-// forward, acc += s rw .* w .* t; transposed, acc += D'_DIR^T (s rw .* w .* u).
-// (rw: coefficient times quadrature weight, w: velocity component DIR at the
-// Gauss points, s = alpha / (r h_DIR).)
-template <typename T, int DIR>
-__device__ __forceinline__ void conv_forward(const T *u, const T *rw, const T *w, T s, T *acc)
-{
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            const int i0 = lidx<DIR>(0, m, n), i1 = lidx<DIR>(1, m, n), i2 = lidx<DIR>(2, m, n);
-            T t0, t1, t2;
-            Q2<T>::deriv(u[i0], u[i1], u[i2], t0, t1, t2);
-            acc[i0] += s * rw[i0] * w[i0] * t0;
-            acc[i1] += s * rw[i1] * w[i1] * t1;
-            acc[i2] += s * rw[i2] * w[i2] * t2;
-        }
-}
-
 // Velocity component DIR times the derivative along DIR, accumulated:
 // cv += s w .* (D'_DIR u), line by line.
 template <typename T, int DIR>
@@ -300,19 +264,6 @@ __device__ __forceinline__ void vel_gradT_acc(const T *z, const T *w, T s, T *ac
         for (int m = 0; m < 3; ++m) {
             const int i0 = lidx<DIR>(0, m, n), i1 = lidx<DIR>(1, m, n), i2 = lidx<DIR>(2, m, n);
             Q2<T>::derivT_acc(s * w[i0] * z[i0], s * w[i1] * z[i1], s * w[i2] * z[i2], acc[i0], acc[i1], acc[i2]);
-        }
-}
-
-template <typename T, int DIR>
-__device__ __forceinline__ void conv_transpose(const T *u, const T *rw, const T *w, T s, T *acc)
-{
-#pragma unroll
-    for (int n = 0; n < 3; ++n)
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            const int i0 = lidx<DIR>(0, m, n), i1 = lidx<DIR>(1, m, n), i2 = lidx<DIR>(2, m, n);
-            Q2<T>::derivT_acc(s * rw[i0] * w[i0] * u[i0], s * rw[i1] * w[i1] * u[i1], s * rw[i2] * w[i2] * u[i2],
-                              acc[i0], acc[i1], acc[i2]);
         }
 }
 
