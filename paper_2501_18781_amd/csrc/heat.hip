@@ -341,7 +341,7 @@ __device__ __forceinline__ void heat_apply_unit(const KMesh &m, const HeatArgs &
                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
                                                 double *partials, const CGDir &dir)
 {
-    constexpr bool TILE = std::is_same<SL, Tile>::value, BRICK = std::is_same<SL, Brick>::value;
+    constexpr bool TILE = std::is_same<SL, Tile>::value, OWNED = std::is_same<SL, Brick>::value;
     constexpr int W = SL::W;
     static_assert(!DIR || (CG && std::is_same<SL, Slab<1>>::value && std::is_same<T, double>::value),
                   "the direction update is CG's");
@@ -444,7 +444,7 @@ __device__ __forceinline__ void heat_apply_unit(const KMesh &m, const HeatArgs &
     }
     __syncthreads(); // phi and the third region no longer read
     double energy = 0.0;
-    if constexpr (BRICK) {
+    if constexpr (OWNED) {
         br.assemble27(u, ps);
         // x.Ax: x_i times the brick's partial sum at node i, with x_i^2 for a
         // Dirichlet node counted once, by the brick that finishes it
@@ -484,12 +484,16 @@ __device__ __forceinline__ void heat_apply_unit(const KMesh &m, const HeatArgs &
     }
 }
 
-template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, typename SL>
-__global__ void __launch_bounds__(SL::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
-                                                            T *__restrict__ y, T *__restrict__ face, CGState *cg,
-                                                            RedWS red)
+// The unit of work of a heat apply kernel: a slab of W sub-bricks, a brick for W = 0.
+constexpr int BRICK = 0;
+template <int W> using Unit = std::conditional_t<W == BRICK, Brick, Slab<W == BRICK ? 1 : W>>;
+
+template <typename T, int MODE, int HK, bool CG, int CONV, bool ISO, int W>
+__global__ void __launch_bounds__(Unit<W>::NT) heat_apply_kernel(KMesh m, HeatArgs a, const T *__restrict__ x,
+                                                                 T *__restrict__ y, T *__restrict__ face, CGState *cg,
+                                                                 RedWS red)
 {
-    heat_apply_unit<T, MODE, HK, CG, CONV, ISO, SL, false>(m, a, x, y, face, cg, red.partials, CGDir{});
+    heat_apply_unit<T, MODE, HK, CG, CONV, ISO, Unit<W>, false>(m, a, x, y, face, cg, red.partials, CGDir{});
 }
 
 template <typename T, int MODE, int HK, int CONV, bool ISO>
@@ -538,7 +542,7 @@ __global__ void __launch_bounds__(BNT * CBW) face_combine_brick_kernel(KMesh m, 
 // slab kernel has finished) and sets alpha = rz / p.Ap, which saves a launch per
 // iteration.  A breakdown sets done here; a workgroup of this launch that then
 // skips its nodes leaves q incomplete, which no later step of the solve reads.
-template <typename T, bool CG, typename SL>
+template <typename T, bool CG, int W>
 __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__restrict__ face, const T *__restrict__ x,
                                                            T *__restrict__ y, CGState *cg,
                                                            const double *__restrict__ partials, unsigned nslabs)
@@ -547,7 +551,7 @@ __global__ void __launch_bounds__(SCT) slab_combine_kernel(KMesh m, const T *__r
         if (cg->done) return;
         if (blockIdx.x == 0) cg_set_alpha<SCT>(cg, partials, nslabs);
     }
-    combine_slabs<T, SL>(m, face, x, y);
+    combine_slabs<T, Unit<W>>(m, face, x, y);
 }
 
 // A brick's slots; those of any slab layout are at most as many (wide_slabs,
@@ -558,23 +562,24 @@ int64_t face_buffer_elems(const KMesh &m) { return n_bricks(m) * BFACE; }
 // (with CG, alpha from the slabs' partials of p.Ap).  With timing on, the
 // events are attached to the slab kernel's own dispatch (they record its
 // start and end, not the neighbouring queue packets).
-template <typename SL, typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
+template <int W, typename T, int MODE, int HK, bool CGF, int CV, bool ISO>
 static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void *x, void *y, void *face, CGState *cg,
                                    const RedWS &r, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
+    using SL = Unit<W>;
     const unsigned ns = (unsigned)n_slabs<SL::W>(m);
     constexpr int NT = SL::NT;
     if (ev0)
-        hipExtLaunchKernelGGL(heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, SL>, dim3(ns), dim3(NT), 0, s, ev0, ev1, 0, m,
+        hipExtLaunchKernelGGL(heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, W>, dim3(ns), dim3(NT), 0, s, ev0, ev1, 0, m,
                               a, (const T *)x, (T *)y, (T *)face, cg, r);
     else
-        heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, SL><<<ns, NT, 0, s>>>(m, a, (const T *)x, (T *)y, (T *)face, cg, r);
+        heat_apply_kernel<T, MODE, HK, CGF, CV, ISO, W><<<ns, NT, 0, s>>>(m, a, (const T *)x, (T *)y, (T *)face, cg, r);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // a single slab shares nothing; alpha from its partial
     if (ns == 1) return CGF ? cg_alpha(cg, &r, ns, s) : hipSuccess;
     constexpr unsigned PER = SCT / combine_lanes<SL>();
-    slab_combine_kernel<T, CGF, SL><<<(ns + PER - 1) / PER, SCT, 0, s>>>(
+    slab_combine_kernel<T, CGF, W><<<(ns + PER - 1) / PER, SCT, 0, s>>>(
         m, (const T *)face, (const T *)x, (T *)y, CGF ? cg : nullptr, CGF ? r.partials : nullptr, CGF ? ns : 0u);
     return hipGetLastError();
 }
@@ -588,29 +593,38 @@ static hipError_t heat_slab_launch(const KMesh &m, const HeatArgs &a, const void
 // 18.4 / 18.0.
 static bool use_tiles(const KMesh &m, const HeatArgs &a) { return Tile::count(m) <= (a.mode == 2 ? 1024 : 2048); }
 
-// Slabs of four sub-bricks or of one (FP64; FP32: slab_width_fp32).  The SIMDs
-// take two wavefronts of these kernels each, so a launch runs in half rounds of
-// 1024 bricks, or of 256 slabs.  Slabs of four shorten the combine pass and use
-// whole lines, but pay for every empty slot along x and for a partly filled last
-// round.  From `lo` bricks on they are taken where they need no more half rounds
-// than single bricks; from `big` on, where the fields outgrow the caches and the
-// lines decide, where enough of their slots hold cells (`filled`).  The forms with more work per cell (a third staged field,
-// the sine Heaviside, whose polynomial only some wavefronts of a slab evaluate)
-// gain least from the combine.  Below three slots of four a slab's slots exceed
-// the face buffer.  Four / one sub-brick, us per apply (half rounds, filled slots):
-//   linear      44^3 (2 / 2, 11 of 12) 17.7 / 18.2, 42x58x47 (3 / 2, 11 of 12) 22.2 / 19.4,
-//               53x70x61 (5 / 4, 14 of 16) 32.6 / 30.2, 64^3 (4 / 4) 30.5 / 32.3, 70^3
-//               (7 / 6) 40.6 / 39.5, 80^3 (8 / 8) 47.3 / 51.3, 104^3 (19 / 18) 105 / 127
-//   per point   57^3 35.2 / 32.4 (15 of 16), 70^3 51.4 / 50.2, 76^3 69.7 / 78.1, 36x200x200
-//               (9 of 12) 266 / 276
-//   sine        57^3 34.1 / 32.0, 64^3 36.1 / 35.7, 88^3 74.2 / 70.3, 96^3 86.8 / 95.1,
-//               36x200x200 178 / 163, 68x160x160 (17 of 20) 199 / 200
-//   convective  57^3 41.9 / 39.6, 70^3 64.1 / 57.5, 80^3 74.8 / 76.6, 82x87x71 (21 of 24)
-//               86.1 / 76.6 (10 / 9), 84^3 100 / 104, 96^3 139 / 164, 36x200x200 272 / 269;
-//               with the sine form 88^3 127 / 129, 91x98x86 (23 of 24) 145 / 151
-//   three phases 57^3 40.7 / 40.4, 70^3 (7 / 6) 60.1 / 56.5, 79x69x75 (7 / 7) 62.0 / 64.2, 80^3
-//               69.5 / 73.4, 36x200x200 238 / 212, 68x160x160 259 / 261; with the sine form
-//               88^3 126 / 118, 96^3 150 / 156, 100^3 (25 of 28) 182 / 176
+// Slabs of four sub-bricks in place of single bricks (FP64; FP32: slab_width_fp32).
+// The SIMDs take two wavefronts of these kernels each, so a launch runs in half
+// rounds of 1024 bricks, or of 256 slabs.  Slabs of four shorten the combine pass
+// and use whole lines, but pay for every empty slot along x and for a partly
+// filled last round.  From `lo` bricks on they are taken where they need no more
+// half rounds than single bricks; from `big` on, where the fields outgrow the
+// caches and the lines decide, where enough of their slots hold cells (`filled`).
+// The forms with more work per cell (a third staged field, the sine Heaviside,
+// whose polynomial only some wavefronts of a slab evaluate) gain least from the
+// combine.  Below three slots of four a slab's slots exceed the face buffer.
+// Four / one sub-brick (three phases and convection: bricks, below), us per apply
+// with three sets of fields in turn (half rounds, filled slots):
+//   linear      46x40x39 (1200 bricks) 18.3 / 17.4, 42x58x47 (3 / 2, 11 of 12) 22.8 /
+//               19.7, 64^3 (4 / 4) 30.4 / 32.2, 53x70x61 (5 / 4, 14 of 16) 32.7 / 30.3,
+//               66x66x64 (6 / 5, 17 of 20) 35.8 / 35.9, 68^3 (6 / 5) 37.1 / 40.2, 80^3 (8 /
+//               8) 53.5 / 64.4, 52x160x160 (13 of 16) 143 / 147, 36x200x200 (9 of 12) 161 /
+//               157
+//   per point   53x70x61 54.1 / 50.4, 64^3 52.2 / 54.7, 72^3 (7 / 6) 73.3 / 72.4, 76^3 (8 /
+//               7) 81.9 / 86.0, 84^3 (11 / 10, 21 of 24) 111 / 109, 106x101x94 176 / 188,
+//               36x200x200 267 / 275
+//   sine        64^3 36.1 / 35.7, 70^3 48.4 / 49.2 (one set: 48.3 / 44.7), 73x68x73 (7 / 6,
+//               19 of 20) 50.8 / 52.5, 84x64x73 (8 / 7, 21 of 24) 55.3 / 56.2, 80^3 60.7 /
+//               67.1, 68x120x120 (17 of 20) 119 / 119, 52x160x160 163 / 152
+//   convective  60^3 (4 / 4) 46.3 / 48.8 (one set: 42.6 / 41.2), 64^3 50.0 / 55.0, 72^3 (7 /
+//               6) 73.5 / 74.6 (one set: 64.4 / 59.2), 76^3 80.3 / 87.9, 52x160x160 236 /
+//               240, 36x200x200 269 / 255; transposed 72^3 73.2 / 72.5, 87x87x69 (10 / 9)
+//               98.2 / 100, 82x84x89 (21 of 24) 115 / 116; sine 80^3 (8 / 8) 96.5 / 104,
+//               87x79x86 (11 / 10) 120 / 117, 92^3 (23 of 24) 142 / 148
+//   three phases 64^3 (4 / 4) 43.3 / 45.7, 70^3 (7 / 6) 62.9 / 62.1, 87x87x69 (22 of 24) 86.9
+//               / 88.8, 84^3 95.9 / 94.9, 36x200x200 240 / 210; with the sine form 87x87x69
+//               111 / 110, 96^3 155 / 158, 105x99x92 (27 of 28) 178 / 178, 118x92x92 (30 of
+//               32) 194 / 183
 // In a CG iteration, whose vectors share the caches and whose single bricks are
 // conv_bricks' (below), the lines lie a little elsewhere.  Slabs of four / bricks,
 // 40 iterations: linear 50x37x61 (3 / 3) 1.77 / 1.70 ms, 61x53x64 (4 / 4) 2.28 / 2.28, 80^3
@@ -622,22 +636,27 @@ static bool wide_slabs(const KMesh &m, const HeatArgs &a, bool cg)
     const int used = (int)ceil_div(m.nx, BB), slots = 4 * (int)ceil_div(m.nx, 4 * BB);
     if (4 * used < 3 * slots) return false;
     const bool sine = a.mode != 1 && a.hkind;
-    int64_t lo = none, big = 13000;
+    int64_t lo = none, big = none;
     bool filled = true;
     if (a.mode == 1) {
-        lo = cg ? 4000 : none;
+        lo = 16 * used > 15 * slots ? 4000 : none;
         big = cg ? 5000 : 6400;
     } else if (a.mode == 2) {
-        lo = sine ? none : 6000;
-        filled = sine ? 16 * used > 15 * slots : 6 * used > 5 * slots;
+        lo = sine ? none : cg ? 6000 : 4000;
+        big = sine || cg ? 13000 : 8500;
+        filled = sine ? 16 * used > 15 * slots : 8 * used > 7 * slots;
     } else if (a.conv) {
-        lo = sine ? none : 8000;
-        big = sine ? 12000 : 9000;
+        lo = sine ? 4000 : 3300;
+        big = sine ? 6500 : a.conv == 2 ? 8600 : 8 * used > 7 * slots ? 6500 : 9000;
+        filled = sine ? 16 * used > 15 * slots : a.conv == 2 ? 8 * used > 7 * slots : 5 * used >= 4 * slots;
+    } else if (sine) {
+        lo = cg ? none : 5400;
+        big = cg ? 9000 : 6000;
         filled = 6 * used > 5 * slots;
     } else {
-        if (cg) big = 9000;
-        if (sine) filled = 6 * used > 5 * slots;
-        else lo = cg ? 3300 : 1200;
+        lo = cg ? 3300 : 1280;
+        big = cg ? 9000 : 4800;
+        filled = 5 * used >= 4 * slots;
     }
     if (nb >= big && filled) return true;
     return nb >= lo && (n_slabs<4>(m) + 255) / 256 <= (nb + 1023) / 1024;
@@ -649,37 +668,37 @@ static bool wide_slabs(const KMesh &m, const HeatArgs &a, bool cg)
 //   three phases 38^3 18.9 / 18.3, 42^3 24.7 / 24.1, 56^3 35.4 / 34.9, 62^3 43.0 / 42.3 (with the
 //               sine form the slab: 56^3 48.3 / 49.4, 45^3 34.9 / 35.1)
 //   convective  44^3 24.8 / 25.0, 40x50x47 (1560 bricks) 25.4 / 25.4, 48^3 27.4 / 26.8, 80x80x20
-//               29.3 / 27.9, 56^3 35.5 / 34.8, 62^3 43.0 / 42.9, 66x73x63 (5168) 53.5 / 54.8, 75x69x73
-//               62.7 / 64.5; transposed 56^3 34.2 / 35.2; from 9000 bricks on, beyond the
-//               caches, where it wastes slots to be a slab of four: 36x200x200 269 / 260,
-//               transposed 265 / 256
+//               29.3 / 27.9, 56^3 35.5 / 34.8, 62^3 43.0 / 42.9; with three sets of fields in turn
+//               63x60x86 (5280) 70.9 / 68.3, 52x160x160 244 / 240; transposed 56^3 34.2 / 35.2, in turn
+//               63x60x86 65.5 / 64.6, 70^3 71.0 / 69.5, 36x200x200 262 / 243
 //   CG, four launches, 40 iterations: linear 42x52x41 1.53 / 1.48 ms, 56^3 2.04 / 1.99; sine 48^3
 //               1.74 / 1.79, 56^3 2.14 / 2.15; per point 53^3 2.06 / 2.05; three phases 56^3 2.44 / 2.39
 static bool conv_bricks(const KMesh &m, int conv) // (three phases and CG: always)
 {
-    const int64_t nb = n_bricks(m);
-    return nb >= 9000 || (conv == 1 && nb >= 1536 && nb < 5000);
+    return n_bricks(m) >= (conv == 1 ? 1536 : 5000);
 }
 
 // Sub-bricks per slab of the FP32 applies.  A brick's FP32 rows of 36 bytes use
 // little of a 128-byte line, and four wavefronts fit a SIMD, so two sub-bricks
 // are better than one from the first mesh that tiles leave, wherever their
 // slots fit the face buffer (not with one or three bricks along x); four where
-// the fields outgrow the last-level cache, if they waste few slots.  One / two
-// / four sub-bricks, and the 4x4x8-cell bricks that were here before slabs:
-// 38^3 cells 14.5 / 13.7 / 15.8 us (14.4), 52^3 20.4 / 17.7 / 19.2 (19.2),
-// 20x80x80 18.8 / 17.8 / 20.3 (17.6), 64^3 26.6 / 23.3 / 23.2 (25.2), 88^3 45.1 /
-// 40.0 / 41.7 (47.6), 128^3 158 / 120 / 108 (155), 36x200x200 (9 of 12 slots) 80.3
-// / 77.8 / 85.6 (84.2); per point 52^3 20.7 / 18.3 / 20.8 (19.9).  The sine form,
-// whose polynomial only some wavefronts evaluate, is better in single bricks
-// while each has a SIMD of its own (38^3 17.2 / 18.3, 44^3 20.1 / 18.9) and where
-// slots stay empty (20x80x80, 5 of 6: 22.1 / 23.6).
+// the fields outgrow the caches, if they waste few slots.  One / two / four
+// sub-bricks, and the 4x4x8-cell bricks that were here before slabs: 38^3 cells
+// 14.5 / 13.7 / 15.8 us (14.4), 52^3 20.4 / 17.7 / 19.2 (19.2), 20x80x80 18.8 / 17.8 /
+// 20.3 (17.6); with three sets of fields in turn 64^3 26.8 / 24.0 / 24.5 (25.4), 87x87x69
+// 39.2 / 35.1 / 36.2 (40.6), 88x82x88 (10164 bricks) 54.2 / 45.3 / 42.6 (54.3), 112^3 110 / 83.3
+// / 77.1 (109), 36x200x200 (9 of 12 slots) 115 / 90.9 / 96.2 (114); per point 52^3 20.7 / 18.3
+// / 20.8 (19.9), 76^3 52.0 / 46.1 / 46.2 (55.8), 86x73x84 (8778) 62.6 / 54.2 / 53.1 (67.5).  The
+// sine form, whose polynomial only some wavefronts evaluate, is better in single
+// bricks while each has a SIMD of its own (38^3 17.2 / 18.3, 44^3 20.1 / 18.9) and where
+// slots stay empty (20x80x80, 5 of 6: 22.1 / 23.6), and gains less from four
+// (88x82x88 51.8 / 52.8 for two / four, 96^3 66.5 / 64.2).
 static int slab_width_fp32(const KMesh &m, const HeatArgs &a)
 {
     const int64_t nb = n_bricks(m);
     const int used = (int)ceil_div(m.nx, BB), slots = 4 * (int)ceil_div(m.nx, 4 * BB);
-    if (nb >= 13000 && 8 * used > 7 * slots) return 4;
     const bool sine = a.mode == 0 && a.hkind;
+    if (sine ? nb >= 13000 && 8 * used > 7 * slots : nb >= (a.mode == 1 ? 8000 : 9700) && 6 * used > 5 * slots) return 4;
     return used == 1 || used == 3 || (sine && (nb <= 1024 || used == 5)) ? 1 : 2;
 }
 
@@ -698,21 +717,21 @@ static hipError_t heat_apply_launch(const KMesh &m, const HeatArgs &a, const voi
             return hipGetLastError();
         }
     }
-#define UNIT_LAUNCH(SL) heat_slab_launch<SL, T, MODE, HK, CGF, CV, ISO>(m, a, x, y, face, cg, r, s, ev0, ev1)
+#define UNIT_LAUNCH(W) heat_slab_launch<W, T, MODE, HK, CGF, CV, ISO>(m, a, x, y, face, cg, r, s, ev0, ev1)
     if constexpr (sizeof(T) == 4) {
         const int w = slab_width_fp32(m, a);
-        if (w == 4) return UNIT_LAUNCH(Slab<4>);
-        if (w == 2) return UNIT_LAUNCH(Slab<2>);
-        return UNIT_LAUNCH(Slab<1>);
+        if (w == 4) return UNIT_LAUNCH(4);
+        if (w == 2) return UNIT_LAUNCH(2);
+        return UNIT_LAUNCH(1);
     } else {
-        if (wide_slabs(m, a, CGF)) return UNIT_LAUNCH(Slab<4>);
+        if (wide_slabs(m, a, CGF)) return UNIT_LAUNCH(4);
         if constexpr (CGF || (MODE == 2 && HK == 0)) {
-            return UNIT_LAUNCH(Brick);
+            return UNIT_LAUNCH(BRICK);
         } else {
             if constexpr (CV != 0) {
-                if (conv_bricks(m, CV)) return UNIT_LAUNCH(Brick);
+                if (conv_bricks(m, CV)) return UNIT_LAUNCH(BRICK);
             }
-            return UNIT_LAUNCH(Slab<1>);
+            return UNIT_LAUNCH(1);
         }
     }
 #undef UNIT_LAUNCH

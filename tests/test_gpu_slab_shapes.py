@@ -86,10 +86,12 @@ def check(n, form, precision=mf.MF_FP64, equal_edges=True, dirichlet=W.FACE_XLO 
 
 # FP32.  Sub-bricks along x, slots of the slabs: 10 of 10 and 5 of 6 and 11 of 12
 # in pairs (the last sub-brick empty), 2 of 2; one and three bricks along x, and
-# the sine form up to 1024 bricks: slabs of one; 13824 bricks and 13248 with 23 of 24 slots: slabs of four
+# the sine form up to 1024 bricks: slabs of one; 13824 bricks, 13248 with 23 of 24
+# slots and 10164 with 21 of 24: slabs of four
 FP32 = [((39, 41, 43), "linear", True), ((18, 61, 70), "linear", False), ((42, 45, 41), "sine", True),
         ((41, 43, 42), "points", True), ((7, 98, 97), "sine", False), ((4, 150, 146), "points", False),
-        ((11, 77, 83), "linear", False), ((38, 40, 39), "sine", True), ((93, 95, 94), "linear", True), ((90, 94, 95), "sine", False)]
+        ((11, 77, 83), "linear", False), ((38, 40, 39), "sine", True), ((93, 95, 94), "linear", True),
+        ((90, 94, 95), "sine", False), ((82, 87, 86), "points", True)]
 
 
 @pytest.mark.parametrize("n,form,equal", FP32)
@@ -98,17 +100,19 @@ def test_fp32(gpu, n, form, equal):
     check(n, form, mf.MF_FP32, equal)
 
 
-# FP64.  Bricks: three phases, the convective form and, beyond 9000 bricks, its
-# transpose; slabs of one; slabs of four in which a sub-brick or more is empty: 11 of
-# 12 slots (1320 bricks), 9 of 12 (13338), 22 of 24 (13200), 18 of 20 (6840), 21
-# of 24 (10164), 19 of 20 (7220), 23 of 24 (13248)
+# FP64.  Bricks: three phases, the convective form and, on large meshes, its
+# transpose; slabs of one; slabs of four in which one to three sub-bricks are
+# empty: 11 of 12 slots (1320 bricks), 13 of 16 (13728), 22 of 24 (13200), 18 of 20
+# (6840), 9 of 12 (7308), 21 of 24 (10164; its transpose bricks), 23 of 24 (11132,
+# 13248), 19 of 20 (7220)
 BRICK = [((38, 41, 35), "melt", False), ((45, 50, 51), "conv", True), ((45, 50, 51), "conv sine", False),
          ((35, 129, 131), "conv", False)]
 ONE = [((42, 58, 47), "linear", False), ((50, 37, 61), "sine", False), ((41, 42, 43), "points", True),
        ((45, 41, 39), "conv", True), ((45, 41, 39), "conv sine", False), ((38, 41, 35), "melt sine", True)]
-FOUR = [((43, 47, 39), "linear", True), ((35, 151, 153), "linear", False), ((86, 98, 95), "sine", True),
-        ((69, 75, 78), "points", False), ((83, 86, 87), "conv", False), ((86, 98, 95), "conv sine", True),
-        ((73, 76, 79), "melt", True), ((91, 95, 96), "melt sine", False)]
+FOUR = [((43, 47, 39), "linear", True), ((50, 127, 129), "linear", False), ((86, 98, 95), "sine", True),
+        ((69, 75, 78), "points", False), ((35, 111, 113), "points", True), ((83, 86, 87), "conv", False),
+        ((90, 86, 87), "conv", True), ((91, 95, 96), "conv sine", True), ((73, 76, 79), "melt", True),
+        ((91, 95, 96), "melt sine", False)]
 
 
 @pytest.mark.parametrize("n,form,equal", BRICK + ONE + FOUR)
